@@ -355,6 +355,22 @@ int ttm_multiply_vjp(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double t
                      const ttm_tt *Cbar, ttm_tt_out *C, double *dA, double *dB, void *ws, size_t ws_bytes,
                      void *stream, ttm_stats *stats);
 
+/* As ttm_multiply_ex and ttm_multiply_vjp, with every truncated SVD by the
+ * block method, whatever its size.  ttm_multiply_ex takes small SVDs by
+ * another method (one workgroup), which gives the same values to the same
+ * accuracy but other rounding errors; a gradient through a truncation
+ * amplifies those by max sigma_1^2 / (sigma_r^2 - sigma_{r+1}^2), so a
+ * caller who compares gradients between versions keeps to one method.  Cbar
+ * of ttm_multiply_block_vjp belongs to the C that ttm_multiply_block gives,
+ * as that of ttm_multiply_vjp to ttm_multiply_ex's: the cores' gauge (signs
+ * of singular vectors among it) is each method's own. */
+int ttm_multiply_block(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol,
+                       ttm_tt_out *C, void *ws, size_t ws_bytes, void *stream,
+                       const ttm_options *opt, ttm_stats *stats);
+int ttm_multiply_block_vjp(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol, const ttm_options *opt,
+                           const ttm_tt *Cbar, ttm_tt_out *C, double *dA, double *dB, void *ws, size_t ws_bytes,
+                           void *stream, ttm_stats *stats);
+
 /* Sizes for conventional_multiply (host only).  The fit keeps the structural
  * bonds capped at chi_out: out_capacity = sum_i c_i d_i c_{i+1} with
  * c_i = min(prod_{k<i} d_k, prod_{k>=i} d_k, chi_out).  TTM_EINVAL when an

@@ -233,7 +233,8 @@ def _run(kind, A, B, chi_out, tol, workspace=None, out=None, stream=None, **opts
     o, keep = _options(trace_cap=trace_cap, **opts)
     L = lib()
     qfn = L.conventional_query if kind == "conv" else L.ttm_query
-    mfn = {"ttm": L.ttm_multiply_ex, "conv": L.conventional_multiply_ex, "static": L.ttm_multiply_static}[kind]
+    mfn = {"ttm": L.ttm_multiply_ex, "conv": L.conventional_multiply_ex, "static": L.ttm_multiply_static,
+           "block": L.ttm_multiply_block}[kind]
     ws_bytes, cap = _query(qfn, A, B, chi_out, o)
     wbuf = None
     if kind != "static":
@@ -431,8 +432,13 @@ def multiply_vjp(A, B, chi_out, tol, Cbar, workspace=None, stream=None, **opts):
     dL/dC), returns (C, dA, dB, stats) with dA, dB the cotangents of A's and
     B's cores (PackedTTs laid out like A and B).  The product C is recomputed
     with every step recorded; ranks are those of that product."""
+    return _vjp(lib().ttm_multiply_vjp, A, B, chi_out, tol, Cbar, workspace, stream, opts)
+
+
+def _vjp(fn, A, B, chi_out, tol, Cbar, workspace, stream, opts):
     import torch
 
+    opts = dict(opts)
     A, B, Cbar = pack(A), pack(B), pack(Cbar)
     _same_device("B", B.data, A.data.device)
     _same_device("Cbar", Cbar.data, A.data.device)
@@ -462,12 +468,12 @@ def multiply_vjp(A, B, chi_out, tol, Cbar, workspace=None, stream=None, **opts):
     dA = torch.zeros_like(A.data)
     dB = torch.zeros_like(B.data)
     st = TtmStats()
-    rc = L.ttm_multiply_vjp(ctypes.byref(A.view), ctypes.byref(B.view), int(chi_out), float(tol), ctypes.byref(o),
-                            ctypes.byref(Cbar.view), ctypes.byref(cout), ctypes.c_void_p(dA.data_ptr()),
-                            ctypes.c_void_p(dB.data_ptr()), ctypes.c_void_p(wbuf.data_ptr()),
-                            ctypes.c_size_t(wbuf.numel()), _stream_handle(stream), ctypes.byref(st))
+    rc = fn(ctypes.byref(A.view), ctypes.byref(B.view), int(chi_out), float(tol), ctypes.byref(o),
+            ctypes.byref(Cbar.view), ctypes.byref(cout), ctypes.c_void_p(dA.data_ptr()),
+            ctypes.c_void_p(dB.data_ptr()), ctypes.c_void_p(wbuf.data_ptr()),
+            ctypes.c_size_t(wbuf.numel()), _stream_handle(stream), ctypes.byref(st))
     if rc != TTM_OK:
-        raise TTMError(rc, "ttm_multiply_vjp")
+        raise TTMError(rc, fn.__name__)
     C = PackedTT(out, list(A.phys), list(bonds), list(offs))
     stats = _stats_dict(st, o)
     del keep
@@ -498,11 +504,13 @@ def _make_inner_loss_function():
         segment at a time), then
         the reverse mode of the product (ttm_multiply_vjp), which recomputes
         the product with every step recorded and undoes the steps, truncated
-        SVDs included.  Only the inputs and C are kept from the forward pass."""
+        SVDs included.  Only the inputs and C are kept from the forward pass.
+        Both directions take every SVD by the block method: the gradient
+        amplifies an SVD's rounding errors, so they stay those of one method."""
 
         @staticmethod
         def forward(ctx, a_data, b_data, A, B, W, chi_out, tol, prec, opts):
-            C, st = multiply(A, B, chi_out, tol, contract_precision=prec, **opts)
+            C, st = _run("block", A, B, chi_out, tol, contract_precision=prec, **opts)
             value, _, _ = inner_grad(W, C, _ones_like_train(C), contract_precision=prec, grads=False)
             ctx.trains = (A, B, W, C, chi_out, tol, prec, opts)
             return torch.tensor(value, dtype=torch.float64, device=a_data.device)
@@ -511,7 +519,9 @@ def _make_inner_loss_function():
         def backward(ctx, g):
             A, B, W, C, chi_out, tol, prec, opts = ctx.trains
             _, dC, _ = inner_grad(W, C, _ones_like_train(C), env_stride=0)
-            _, dA, dB, _ = multiply_vjp(A, B, chi_out, tol, dC, contract_precision=prec, **opts)
+            opts = dict(opts, contract_precision=prec)
+            _, dA, dB, _ = _vjp(lib().ttm_multiply_block_vjp, A, B, chi_out, tol, dC, opts.pop("workspace", None),
+                                opts.pop("stream", None), opts)
             return g * dA.data, g * dB.data, None, None, None, None, None, None, None
 
     return TTMInnerLoss

@@ -145,6 +145,15 @@ PROTOTYPES = {
                                         ctypes.POINTER(TtmTTOut), ctypes.c_void_p, ctypes.c_void_p,
                                         ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
                                         ctypes.POINTER(TtmStats)]),
+    "ttm_multiply_block": (ctypes.c_int, [ctypes.POINTER(TtmTT), ctypes.POINTER(TtmTT), ctypes.c_int32,
+                                          ctypes.c_double, ctypes.POINTER(TtmTTOut), ctypes.c_void_p,
+                                          ctypes.c_size_t, ctypes.c_void_p, ctypes.POINTER(TtmOptions),
+                                          ctypes.POINTER(TtmStats)]),
+    "ttm_multiply_block_vjp": (ctypes.c_int, [ctypes.POINTER(TtmTT), ctypes.POINTER(TtmTT), ctypes.c_int32,
+                                              ctypes.c_double, ctypes.POINTER(TtmOptions), ctypes.POINTER(TtmTT),
+                                              ctypes.POINTER(TtmTTOut), ctypes.c_void_p, ctypes.c_void_p,
+                                              ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
+                                              ctypes.POINTER(TtmStats)]),
     "ttm_strerror": (ctypes.c_char_p, [ctypes.c_int]),
     "ttm_last_error": (ctypes.c_char_p, []),
     "ttm_version": (ctypes.c_char_p, []),

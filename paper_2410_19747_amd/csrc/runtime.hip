@@ -74,6 +74,7 @@ struct Options {
   int svd_mode = TTM_SVD_JACOBI;
   int rsvd_power = 10;
   double rsvd_tol = 2e-8;
+  bool block_svd = false;  // ttm_multiply_block: every SVD by the block method
 };
 
 // Largest matrix a QR or SVD step takes: each side at most 2^30 (the kernels
@@ -532,6 +533,12 @@ struct Runner {
     note(nxt.s);
   }
 
+  SvdPlan plan_svd(int np, int no) const {
+    SvdPlan p = svd_plan(np, no);
+    if (o.block_svd) p.small = false;
+    return p;
+  }
+
   // ---- one truncated SVD (svd_oside) with the bookkeeping of the rule of
   // Eq. (eps): forced ranks, traces, discarded weight and the flop model.
   // Returns the rank, or -1 after setting err.
@@ -623,7 +630,7 @@ struct Runner {
     }
     const int Dl = P.s.rl, dp = P.s.d, Dm = P.s.rr, dx = X.s.d, Dr = X.s.rr;
     const int m = Dl * dx, n = dp * Dr;
-    const SvdPlan sp = svd_plan(m, n);
+    const SvdPlan sp = plan_svd(m, n);
     TapeEntry e;
     SvdAll all;
     if (tape) {
@@ -711,7 +718,7 @@ struct Runner {
     const int m = Dl * dx, n = dp * Dr;
     // Theta row-major (m x n) is the column-major n x m matrix Theta^T, whose
     // right singular vectors are Theta's left ones.
-    const SvdPlan sp = svd_plan(n, m);
+    const SvdPlan sp = plan_svd(n, m);
     double *Y = wbuf;
     double *sws = wbuf + ((((int64_t)m * n) + 31) & ~(int64_t)31);
     GemmArgs g;
@@ -788,7 +795,7 @@ struct Runner {
     const int m = cur.s.rl * cur.s.d, n = cur.s.rr;
     // The row-major m x n core is the column-major n x m matrix Y = Pi_i^T,
     // whose right singular vectors are Pi_i's left ones.
-    const SvdPlan sp = svd_plan(n, m);
+    const SvdPlan sp = plan_svd(n, m);
     TapeEntry e;
     SvdAll all;
     if (tape) {
@@ -1000,10 +1007,11 @@ int run_ttm_impl(const ttm_tt *A, const ttm_tt *B, int chi_out, double tol, ttm_
 // schedule of run_ttm with every step's operands copied into `tape`.
 int run_ttm_taped(const ttm_tt *A, const ttm_tt *B, int chi_out, double tol, const ttm_options *opt,
                   ttm_tt_out *C, void *ws, size_t ws_bytes, hipStream_t st, ttm_stats *stats, Tape *tape,
-                  bool *swapped) {
+                  bool *swapped, bool block_svd) {
   Options o;
   int e = resolve_options(opt, chi_out, o);
   if (e) return e;
+  o.block_svd = block_svd;
   // the reverse mode differentiates the full SVD's truncation only
   if (o.gauge != TTM_GAUGE_MOVING || o.svd_mode != TTM_SVD_JACOBI) return TTM_EUNSUPPORTED;
   *swapped = moves_first(A, B, o);
@@ -1419,9 +1427,9 @@ int ttm_query(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, const ttm_optio
   return TTM_OK;
 }
 
-int ttm_multiply_ex(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol, ttm_tt_out *C,
-                    void *ws, size_t ws_bytes, void *stream, const ttm_options *opt,
-                    ttm_stats *stats) {
+static int multiply_checked(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol, ttm_tt_out *C,
+                            void *ws, size_t ws_bytes, void *stream, const ttm_options *opt,
+                            ttm_stats *stats, bool block_svd) {
   ttm::clear_last_error();
   int e = ttm::validate_pair(A, B);
   if (e) return e;
@@ -1430,7 +1438,20 @@ int ttm_multiply_ex(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double to
   ttm::Options o;
   e = ttm::resolve_options(opt, chi_out, o);
   if (e) return e;
+  o.block_svd = block_svd;
   return ttm::run_ttm(A, B, chi_out, tol, C, ws, ws_bytes, static_cast<hipStream_t>(stream), o, stats);
+}
+
+int ttm_multiply_ex(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol, ttm_tt_out *C,
+                    void *ws, size_t ws_bytes, void *stream, const ttm_options *opt,
+                    ttm_stats *stats) {
+  return multiply_checked(A, B, chi_out, tol, C, ws, ws_bytes, stream, opt, stats, false);
+}
+
+int ttm_multiply_block(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol, ttm_tt_out *C,
+                       void *ws, size_t ws_bytes, void *stream, const ttm_options *opt,
+                       ttm_stats *stats) {
+  return multiply_checked(A, B, chi_out, tol, C, ws, ws_bytes, stream, opt, stats, true);
 }
 
 int ttm_multiply(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol, ttm_tt_out *C,

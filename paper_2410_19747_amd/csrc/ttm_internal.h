@@ -228,6 +228,7 @@ hipError_t launch_frob_from_norms(const double *x, int n, double *result, hipStr
 // Y itself.
 struct SvdPlan {
   int np = 0, no = 0, k = 0;
+  bool small = false;  // the one-workgroup path (launch_svd_small)
   JacobiPlan jp;
 };
 SvdPlan svd_plan(int np, int no, int force_bw = 0);
@@ -262,6 +263,33 @@ struct SvdAll {
   double *sigma = nullptr;  // k doubles, decreasing
   int kg = 0;               // out
 };
+// The SVD's last part, or all of it, in one launch (kernels_svd_small.hip):
+// from Y itself when both sides are at most kSvdSmallSide (SMALL_Y), or from
+// the triangular factor R of a QR whose smaller side is (SMALL_RT: Jacobi on
+// R^T, whose normalised columns are the vectors over R's columns; SMALL_RTQ:
+// QR of R^T = Q2 R2 first, the vectors over R's rows).
+constexpr int kSvdSmallSide = 128;
+enum { SMALL_Y = 0, SMALL_RT = 1, SMALL_RTQ = 2 };
+struct SvdSmall {
+  int mode = SMALL_Y;
+  const double *src = nullptr;  // Y (np x no) or S with R in its upper triangle, column-major
+  int64_t ld = 0;               // its column stride
+  int np = 0, no = 0, k = 0;
+  const int *rowperm = nullptr; // SMALL_RT: column j of R stands for row rowperm[j] of U
+  double eps = 0.0;
+  int cap = 0, forced = 0, max_sweeps = 0;
+  const double *full_total = nullptr;
+  double *u = nullptr;          // U_r: entry (o, t) at o u_os + t u_ts (u_os = 0: at o r + t), or null
+  int64_t u_os = 0, u_ts = 0;
+  double *uall = nullptr;       // every resolved vector (at least U_r), column-major, or null
+  int64_t uall_ld = 0;
+  double *sig = nullptr;        // the k singular values, decreasing, or null
+  double *result = nullptr;     // as JacobiBufs::result, and [7] = sweeps (negative: not converged)
+};
+hipError_t launch_svd_small(const SvdSmall &q, hipStream_t s);
+// dst (no x nc, column-major) = src (k x nc, column-major), rows k .. no - 1 zero.
+hipError_t launch_embed_rows(double *dst, const double *src, int k, int no, int nc, hipStream_t s);
+
 // full_total (device, optional): the squared Frobenius norm of a larger
 // matrix of which Y is a projection; the rank rule then counts the weight
 // outside Y, full_total - ||Y||_F^2, as part of every tail (randomized SVD).
@@ -345,7 +373,7 @@ struct Tape {
 // traded places (move_factor = TTM_MOVE_SMALLER).
 int run_ttm_taped(const ttm_tt *A, const ttm_tt *B, int chi_out, double tol, const ttm_options *opt,
                   ttm_tt_out *C, void *ws, size_t ws_bytes, hipStream_t st, ttm_stats *stats, Tape *tape,
-                  bool *swapped);
+                  bool *swapped, bool block_svd);
 // Sizes for the reverse mode (host only).
 int vjp_sizes(const ttm_tt *A, const ttm_tt *B, int chi_out, const ttm_options *opt, size_t *fwd_ws,
               int64_t *tape_doubles, int64_t *max_core, int64_t *max_mn, int64_t *out_capacity);

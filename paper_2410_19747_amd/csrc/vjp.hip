@@ -250,7 +250,7 @@ int vjp_layout(const ttm_tt *A, const ttm_tt *B, int chi_out, const ttm_options 
 
 int run_vjp(const ttm_tt *A, const ttm_tt *B, int chi_out, double tol, const ttm_options *opt, const ttm_tt *Cbar,
             ttm_tt_out *C, double *dA, double *dB, void *ws, size_t ws_bytes, hipStream_t st, ttm_stats *stats,
-            bool &enqueued) {
+            bool &enqueued, bool block_svd) {
   VjpLayout L;
   int64_t cap = 0;
   int e = vjp_layout(A, B, chi_out, opt, L, &cap);
@@ -267,7 +267,7 @@ int run_vjp(const ttm_tt *A, const ttm_tt *B, int chi_out, double tol, const ttm
   tape.cap = L.tape / 8;
   bool swapped = false;
   enqueued = true;
-  e = run_ttm_taped(A, B, chi_out, tol, opt, C, ws, L.fwd, st, stats, &tape, &swapped);
+  e = run_ttm_taped(A, B, chi_out, tol, opt, C, ws, L.fwd, st, stats, &tape, &swapped, block_svd);
   if (e) return e;
   for (int i = 0; i < n; ++i)
     if (Cbar->phys[i] != A->phys[i] || Cbar->bonds[i] != C->bonds[i]) return TTM_ESHAPE;
@@ -403,15 +403,29 @@ extern "C" int ttm_vjp_query(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, 
   return TTM_OK;
 }
 
-extern "C" int ttm_multiply_vjp(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol,
-                                const ttm_options *opt, const ttm_tt *Cbar, ttm_tt_out *C, double *dA, double *dB,
-                                void *ws, size_t ws_bytes, void *stream, ttm_stats *stats) {
+namespace {
+int vjp_checked(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol, const ttm_options *opt,
+                const ttm_tt *Cbar, ttm_tt_out *C, double *dA, double *dB, void *ws, size_t ws_bytes, void *stream,
+                ttm_stats *stats, bool block_svd) {
   ttm::clear_last_error();
   if (!(tol >= 0.0) || !isfinite(tol)) return TTM_EINVAL;
   if (opt && opt->profile != 0) return TTM_EINVAL;
   bool enqueued = false;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int e = ttm::run_vjp(A, B, chi_out, tol, opt, Cbar, C, dA, dB, ws, ws_bytes, st, stats, enqueued);
+  const int e = ttm::run_vjp(A, B, chi_out, tol, opt, Cbar, C, dA, dB, ws, ws_bytes, st, stats, enqueued, block_svd);
   if (e != TTM_OK && enqueued) (void)hipStreamSynchronize(st);
   return e;
+}
+}  // namespace
+
+extern "C" int ttm_multiply_vjp(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol,
+                                const ttm_options *opt, const ttm_tt *Cbar, ttm_tt_out *C, double *dA, double *dB,
+                                void *ws, size_t ws_bytes, void *stream, ttm_stats *stats) {
+  return vjp_checked(A, B, chi_out, tol, opt, Cbar, C, dA, dB, ws, ws_bytes, stream, stats, false);
+}
+
+extern "C" int ttm_multiply_block_vjp(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double tol,
+                                      const ttm_options *opt, const ttm_tt *Cbar, ttm_tt_out *C, double *dA,
+                                      double *dB, void *ws, size_t ws_bytes, void *stream, ttm_stats *stats) {
+  return vjp_checked(A, B, chi_out, tol, opt, Cbar, C, dA, dB, ws, ws_bytes, stream, stats, true);
 }
