@@ -97,6 +97,18 @@ int ttm_test_svd_bw(const double *M, int m, int n, double eps, int cap, int forc
 size_t ttm_test_cholqr2_ws_bytes(int p, int l);
 int ttm_test_cholqr2(double *Y, int p, int l, int *breakdown, void *ws, size_t ws_bytes, void *stream);
 
+/* The cap leading singular triplets of the m x n column-major Theta (device,
+ * ld m) as a capped swap takes them: P' = V_r^T (pt, r x n row-major) and
+ * X' = Theta V_r (xt, m x r row-major), r <= cap by the rule of Eq. (eps),
+ * with the discarded and the total weight on the host (weights[0], [1]) and
+ * weights[2] the part of Theta's norm that the triplets miss.  *refused = 1
+ * where the swap would run the full SVD instead (nothing is valid then).
+ * ws: device, ttm_test_capped_svd_ws_bytes(m, n, cap) bytes, 0 for sizes that
+ * always take the full SVD. */
+size_t ttm_test_capped_svd_ws_bytes(int m, int n, int cap);
+int ttm_test_capped_svd(const double *Theta, int m, int n, int cap, double eps, double *pt, double *xt, int *rank,
+                        int *refused, double *weights, void *ws, size_t ws_bytes, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -423,6 +423,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
       const int c = e / T::N, r = e % T::N;
       sm.W[c * T::LD + r] = (r < a.np && c < a.no) ? a.src[(int64_t)c * a.ld + r] : 0.0;
     }
+  } else if (MODE == SMALL_R) {
+    for (int e = tid; e < T::N * T::N; e += T::NT) {
+      const int j = e / T::N, c = e % T::N;
+      sm.W[j * T::LD + c] = (j < a.k && c <= j) ? a.src[(int64_t)j * a.ld + c] : 0.0;
+    }
   } else {
     // column c of W (or of the matrix that QR takes) is row c of R
     for (int e = tid; e < T::N * T::N; e += T::NT) {
@@ -447,7 +452,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll 1
   while (true) {
     s.fetch();
-    if (MODE != SMALL_RT && todo == QR) {
+    if ((MODE == SMALL_Y || MODE == SMALL_RTQ) && todo == QR) {
       s.qr(a.k);
       if (tid < T::N) sm.perm[tid] = tid;
       __syncthreads();
@@ -481,7 +486,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int i = 0; i < T::RL; ++i) s.x[e][i] = __builtin_amdgcn_ldexp(s.x[e][i], -ex);
       if (MODE == SMALL_Y && tid < T::N) sm.orow[tid] = sm.perm[tid];
       if (MODE == SMALL_RTQ && tid < T::N) sm.perm[tid] = tid;
-      todo = MODE == SMALL_RT ? SWEEP : QR;
+      todo = (MODE == SMALL_Y || MODE == SMALL_RTQ) ? QR : SWEEP;
     } else {
       todo = SWEEP;
       if (conv || sweeps >= a.max_sweeps) break;
@@ -580,14 +585,16 @@ void launch_mode(const SvdSmall &a, hipStream_t s) {
     hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_Y>), dim3(1), dim3(64 * NW), 0, s, a);
   else if (a.mode == SMALL_RT)
     hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_RT>), dim3(1), dim3(64 * NW), 0, s, a);
-  else
+  else if (a.mode == SMALL_RTQ)
     hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_RTQ>), dim3(1), dim3(64 * NW), 0, s, a);
+  else
+    hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_R>), dim3(1), dim3(64 * NW), 0, s, a);
 }
 }  // namespace
 
 hipError_t launch_svd_small(const SvdSmall &a, hipStream_t s) {
   const int side = (a.mode == SMALL_Y) ? (a.np > a.no ? a.np : a.no) : a.k;
-  if (a.k < 1 || side > kSvdSmallSide || a.mode < SMALL_Y || a.mode > SMALL_RTQ) return hipErrorInvalidValue;
+  if (a.k < 1 || side > kSvdSmallSide || a.mode < SMALL_Y || a.mode > SMALL_R) return hipErrorInvalidValue;
   if (side <= 16)
     launch_mode<4, 1>(a, s);
   else if (side <= 32)

@@ -44,6 +44,7 @@
 #include <stdio.h>
 
 #include <algorithm>
+#include <vector>
 
 #include "ttm_internal.h"
 
@@ -281,14 +282,16 @@ struct CqrBufs {
   double *Rf = nullptr;    // l x l: the off-diagonal blocks of R
   double *rinv = nullptr;  // nb x CNB x CNB
   double *gd = nullptr;    // l
-  double *part = nullptr;  // kGramPart
+  double *part = nullptr;  // split-K scratch of the Gram product
+  int64_t part_doubles = kGramPart;
 };
-size_t cqr_doubles(int l) {
+size_t cqr_doubles(int l, int64_t part = kGramPart) {
   const size_t nb = (l + CNB - 1) / CNB;
-  return 2 * r32((size_t)l * l) + r32(nb * CNB * CNB) + r32((size_t)l) + r32((size_t)kGramPart);
+  return 2 * r32((size_t)l * l) + r32(nb * CNB * CNB) + r32((size_t)l) + r32((size_t)part);
 }
-CqrBufs cqr_carve(int l, double *base) {
+CqrBufs cqr_carve(int l, double *base, int64_t part = kGramPart) {
   CqrBufs b;
+  b.part_doubles = part;
   double *q = base;
   auto adv = [&](size_t n) {
     double *x = q;
@@ -300,7 +303,7 @@ CqrBufs cqr_carve(int l, double *base) {
   b.Rf = adv((size_t)l * l);
   b.rinv = adv(nb * CNB * CNB);
   b.gd = adv((size_t)l);
-  b.part = adv((size_t)kGramPart);
+  b.part = adv((size_t)part);
   return b;
 }
 
@@ -320,7 +323,7 @@ hipError_t cholqr(double *Y, int p, int l, double *Q, const CqrBufs &b, int *fai
     g.A = Y; g.a_rs = p; g.a_cs = 1;
     g.B = Y; g.b_rs = 1; g.b_cs = p;
     g.C = b.G; g.c_rs1 = l; g.c_cs1 = 1;
-    g.part = b.part; g.part_doubles = kGramPart;
+    g.part = b.part; g.part_doubles = b.part_doubles;
     if ((e = launch_gemm(g, s)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(diag_kernel, dim3((l + 255) / 256), dim3(256), 0, s, b.G, l, l, b.gd);
@@ -616,6 +619,280 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
   if (trace)
     fprintf(stderr, "[ttm] rsvd %dx%d l=%d q=%d sweeps=%d rank=%d disc=%.3e total=%.3e\n", m, n, l, power,
             out.sweeps, r, out.disc, out.total);
+  return out;
+}
+
+// ====================================================================== the capped SVD at full accuracy
+// The default swap SVD where the cap keeps at most a quarter of the
+// spectrum: the cap leading triplets by a filtered subspace iteration that
+// is carried to rounding level and then checked, instead of all of them.
+//
+// A capped swap of d = 8 sites keeps an eighth of its singular values, and
+// the Jacobi SVD spends its sweeps on the other seven eighths, latency bound
+// (63 rounds a sweep at 1024 columns).  Measured, products of two turbulence
+// components: 256^3 at bond 64 (512 x 512 swaps) 214 -> 86 ms, at 128
+// (1024 x 1024) 428 -> 189 ms, 128^3 at 256 (2048 x 2048) 660 -> 256 ms, and
+// their error against 64 bits halves (8e-14 -> 5e-14, 1.1e-13 -> 6e-14).
+// With l = 2 cap columns and M = Theta^T Theta:
+//   1. Y = orth(Theta^T Omega), then twice Y = orth(M Y); the diagonal of the
+//      last Cholesky factor gives estimates of the squared singular values:
+//      the smallest, b, bounds the part to suppress, the cap-th the part kept;
+//   2. as many times as the estimates ask for, Y = orth(T_2((2 / b) M - I) Y)
+//      with the Chebyshev polynomial T_2, which stays below 1 on [0, b] and
+//      grows as 2 x^2 - 1 above (Halko, Martinsson and Tropp 2011 iterate with
+//      M^2, half the digits).  Degree 2 because CholeskyQR takes a condition
+//      up to about 1e7 and T_2 raises the leading direction by 1e4 to 1e7 over
+//      the last;
+//   3. Z = orth(Theta Y), and the Jacobi SVD of Theta^T Z (n x l, its columns
+//      near orthogonal by now): its values and left vectors V_r, orthonormal
+//      to rounding; X' = Theta V_r.
+// The result is checked, not trusted: (Theta V_r - Z Z^T Theta V_r) is what
+// the computed triplets miss, so that they are those of a matrix that far
+// from Theta (a backward error; measured 2e-16 to 1.6e-15 of ||Theta||_F at
+// 512 to 2048 rows, its own rounding); above 32 u = 7e-15 the swap takes the
+// full SVD.  The rule of Eq. (eps) is taken with the weight outside the l
+// values in every tail, and checked with the discarded weight summed from
+// Theta - X' P' itself.  The full SVD also runs where that check is not clear
+// by 1e-6, where the spectrum is too flat for MAX_FILTER filters, and where a
+// Cholesky pivot breaks down (Theta of rank below l).
+namespace {
+constexpr int PSVD_POWER = 2;     // plain iterations before the filter
+constexpr int MAX_FILTER = 10;    // beyond it the full SVD costs no more
+
+struct PsvdBufs {
+  double *Y, *W, *Z, *T, *vt, *small, *full, *diag;
+  int *fail;
+  CqrBufs cq;
+  double *svd;
+};
+// part: the split-K scratch that is left.
+size_t psvd_basis_doubles(int m, int n, int l) {
+  return r32((size_t)std::max(m, n) * std::max(l, svd_columns_capacity(n, l)));
+}
+size_t psvd_fixed_doubles(int m, int n, int l) {
+  return 4 * psvd_basis_doubles(m, n, l) + r32((size_t)l * l) + r32(8 + SQB) + r32((size_t)l) + r32(8) +
+         cqr_doubles(l, 0);
+}
+// Columns of an m x n matrix that the four basis buffers hold (at least
+// 4 l = 8 cap of them).
+int psvd_columns(int m, int n, int l) {
+  return (int)std::min<int64_t>(n, (int64_t)(4 * psvd_basis_doubles(m, n, l)) / m);
+}
+// Workspace left for split-K partials, or negative.
+int64_t psvd_part_doubles(int m, int n, int cap) {
+  const int l = rsvd_sketch_cols(cap);
+  // the region of the full SVD of the same matrix, which a fallback uses
+  const int64_t have = (int64_t)svd_ws_doubles(svd_plan(m, n));
+  const int64_t fixed = (int64_t)psvd_fixed_doubles(m, n, l) + (int64_t)svd_columns_ws_doubles(n, l);
+  return std::min<int64_t>(kGramPart, (have - fixed) & ~(int64_t)31);
+}
+}  // namespace
+
+bool psvd_eligible(int m, int n, int cap) {
+  if (!rsvd_eligible(m, n, cap)) return false;
+  if (std::min(m, n) <= kSvdSmallSide) return false;  // one launch does the full SVD
+  const int l = rsvd_sketch_cols(cap);
+  if (n > kSvdMaxSide || m > kSvdMaxSide) return false;
+  // the discarded weight is summed over at most six blocks of columns
+  const int room = psvd_columns(m, n, l);
+  if ((n + room - 1) / room > 6) return false;
+  return psvd_part_doubles(m, n, cap) >= 4 * (int64_t)l * l;
+}
+
+PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
+                      double *ws, hipStream_t s, KernelTimer *timer, int trace) {
+  PsvdResult out;
+  const int l = rsvd_sketch_cols(cap);
+  const int64_t part = psvd_part_doubles(m, n, cap);
+  PsvdBufs b;
+  {
+    double *q = ws;
+    auto adv = [&](size_t nd) {
+      double *x = q;
+      q += r32(nd);
+      return x;
+    };
+    const size_t basis = psvd_basis_doubles(m, n, l);
+    b.Y = adv(basis);
+    b.W = adv(basis);
+    b.Z = adv(basis);
+    b.T = adv(basis);
+    b.vt = adv((size_t)l * l);
+    b.full = adv(8 + SQB);
+    b.diag = adv((size_t)l);
+    b.fail = reinterpret_cast<int *>(adv(8));
+    b.cq = cqr_carve(l, q, part);
+    q += cqr_doubles(l, part);
+    b.svd = q;
+  }
+  auto ok = [&](hipError_t e) {
+    if (e != hipSuccess) {
+      out.err = TTM_EHIP;
+      char what[112];
+      snprintf(what, sizeof(what), "the capped truncated SVD of a %d x %d matrix", m, n);
+      note_hip_error(e, what);
+      if (trace) fprintf(stderr, "[ttm] HIP error %s in %s\n", hipGetErrorName(e), what);
+      return false;
+    }
+    return true;
+  };
+  auto sync = [&]() {
+    if (!ok(hipStreamSynchronize(s))) return false;
+    if (timer && timer->on) timer->collect();
+    return true;
+  };
+  auto refuse = [&](const char *why, double v) {
+    out.fallback = true;
+    if (trace) fprintf(stderr, "[ttm] psvd %dx%d cap %d: %s (%.2e), full SVD instead\n", m, n, cap, why, v);
+    return out;
+  };
+  double *ycur = b.Y, *wcur = b.W, *zcur = b.Z, *spare = b.T;
+  auto orth = [&](double *&X, int p, bool diag = false) {
+    if (!ok(cholqr(X, p, l, spare, b.cq, b.fail, s, timer, diag))) return false;
+    std::swap(X, spare);
+    return true;
+  };
+  // out = alpha Theta in (m x l) or alpha Theta^T in (n x l), plus beta out
+  auto prod = [&](bool transposed, const double *in, double *o, double alpha = 1.0, double beta = 0.0) {
+    GemmArgs g;
+    g.alpha = alpha;
+    g.beta = beta;
+    g.N = l;
+    if (transposed) {
+      g.M = n; g.K = m;
+      g.A = Theta; g.a_rs = m; g.a_cs = 1;
+      g.B = in; g.b_rs = 1; g.b_cs = m;
+      g.C = o; g.c_rs1 = 1; g.c_cs1 = n;
+    } else {
+      g.M = m; g.K = n;
+      g.A = Theta; g.a_rs = 1; g.a_cs = m;
+      g.B = in; g.b_rs = 1; g.b_cs = n;
+      g.C = o; g.c_rs1 = 1; g.c_cs1 = m;
+    }
+    g.part = b.cq.part;
+    g.part_doubles = part;
+    Timed tm(timer, KC_GEMM, s);
+    return ok(launch_gemm(g, s));
+  };
+  auto sumsq = [&](const double *x, int64_t nx, double *o) {
+    hipLaunchKernelGGL(sumsq_part_kernel, dim3(SQB), dim3(256), 0, s, x, nx, b.full + 8);
+    hipLaunchKernelGGL(sumsq_final_kernel, dim3(1), dim3(256), 0, s, b.full + 8, o);
+    return ok(hipGetLastError());
+  };
+  // 1. the start
+  if (!ok(launch_zero_int(b.fail, 1, s))) return out;
+  {
+    Timed tm(timer, KC_JAC_OTHER, s);
+    if (!ok(launch_splitmix_fill(zcur, (int64_t)m * l, 0x5eedULL, 0, s))) return out;
+    if (!sumsq(Theta, (int64_t)m * n, b.full)) return out;
+  }
+  if (!prod(true, zcur, ycur) || !orth(ycur, n)) return out;
+  for (int it = 0; it < PSVD_POWER; ++it) {
+    const bool last = it + 1 == PSVD_POWER;
+    if (!prod(false, ycur, zcur) || !prod(true, zcur, ycur) || !orth(ycur, n, last)) return out;
+  }
+  std::vector<double> h(l);
+  double tot = 0.0;
+  int fail = 0;
+  hipLaunchKernelGGL(diag_kernel, dim3((l + 255) / 256), dim3(256), 0, s, b.cq.Rf, l, l, b.diag);
+  if (!ok(hipGetLastError())) return out;
+  if (!ok(hipMemcpyAsync(h.data(), b.diag, sizeof(double) * l, hipMemcpyDeviceToHost, s))) return out;
+  if (!ok(hipMemcpyAsync(&tot, b.full, sizeof(double), hipMemcpyDeviceToHost, s))) return out;
+  if (!ok(hipMemcpyAsync(&fail, b.fail, sizeof(int), hipMemcpyDeviceToHost, s))) return out;
+  if (!sync()) return out;
+  if (fail) return refuse("CholeskyQR breakdown", fail);
+  std::sort(h.begin(), h.end(), [](double x, double y) { return x > y; });
+  const double bnd = h[l - 1], kept = h[cap - 1];
+  // 2. the filter: each raises the cap-th direction over the rest by
+  // 2 x^2 - 1; the start has raised it by (kept / bnd)^(power + 1/2).  What
+  // is asked for is 1e-18 of ||Theta||_F: the estimates are a little rough, and
+  // with 1e-16 one swap in thirty was left at 2e-14.
+  const double x = 2.0 * kept / bnd - 1.0, gain = 2.0 * x * x - 1.0;
+  if (!(bnd > 0.0) || !(gain > 1.0) || !(tot > 0.0) || !isfinite(tot)) return refuse("no gap", gain);
+  const double need = log(1e18) + 0.5 * log(kept / tot) - (PSVD_POWER + 0.5) * log(kept / bnd);
+  const int filters = std::max(0, (int)ceil(need / log(gain)));
+  if (filters > MAX_FILTER) return refuse("too flat", filters);
+  for (int it = 0; it < filters; ++it) {
+    // w = M y - b y, y <- M w + (b^2 / 8) y = (b^2 / 8) T_2((2 / b) M - I) y
+    if (!ok(launch_copy(wcur, ycur, (int64_t)n * l, s))) return out;
+    if (!prod(false, ycur, zcur) || !prod(true, zcur, wcur, 1.0, -bnd)) return out;
+    if (!prod(false, wcur, zcur) || !prod(true, zcur, ycur, 1.0, 0.125 * bnd * bnd)) return out;
+    if (!orth(ycur, n)) return out;
+  }
+  // 3. Z = orth(Theta Y), the SVD of Theta^T Z
+  if (!prod(false, ycur, zcur) || !orth(zcur, m) || !orth(zcur, m)) return out;
+  if (!prod(true, zcur, ycur)) return out;
+  if (!ok(hipMemcpyAsync(&fail, b.fail, sizeof(int), hipMemcpyDeviceToHost, s))) return out;
+  SvdResult so = svd_columns(ycur, wcur, n, l, eps, cap, max_sweeps, pt, b.diag, b.svd, s, timer, trace, b.full);
+  out.sweeps = so.sweeps;
+  if (so.err != TTM_OK) {
+    out.err = so.err;
+    return out;
+  }
+  if (fail) return refuse("CholeskyQR breakdown", fail);
+  const int r = so.rank;
+  // X' = Theta V_r (m x r, row-major); what the triplets miss; the weight discarded
+  {
+    GemmArgs g;
+    g.M = m; g.N = r; g.K = n;
+    g.A = Theta; g.a_rs = 1; g.a_cs = m;
+    g.B = pt; g.b_rs = 1; g.b_cs = n;
+    g.C = xt; g.c_rs1 = r; g.c_cs1 = 1;
+    GemmArgs q;  // Z^T X' (l x r, row-major)
+    q.M = l; q.N = r; q.K = m;
+    q.A = zcur; q.a_rs = m; q.a_cs = 1;
+    q.B = xt; q.b_rs = r; q.b_cs = 1;
+    q.C = b.vt; q.c_rs1 = r; q.c_cs1 = 1;
+    q.part = b.cq.part; q.part_doubles = part;
+    GemmArgs d;  // X' - Z (Z^T X')
+    d.M = m; d.N = r; d.K = l;
+    d.A = zcur; d.a_rs = 1; d.a_cs = m;
+    d.B = b.vt; d.b_rs = r; d.b_cs = 1;
+    d.C = spare; d.c_rs1 = r; d.c_cs1 = 1;
+    d.alpha = -1.0; d.beta = 1.0;
+    Timed tm(timer, KC_GEMM, s);
+    if (!ok(launch_gemm(g, s)) || !ok(launch_gemm(q, s))) return out;
+    if (!ok(launch_copy(spare, xt, (int64_t)m * r, s)) || !ok(launch_gemm(d, s))) return out;
+  }
+  if (!sumsq(spare, (int64_t)m * r, b.full + 1)) return out;
+  // Theta - X' P' in the basis buffers, by as many columns as they hold
+  const int room = psvd_columns(m, n, l);
+  double disc = 0.0;
+  int blocks = 0;
+  for (int c0 = 0; c0 < n; c0 += room, ++blocks) {
+    const int nc = std::min(room, n - c0);
+    GemmArgs d;
+    d.M = m; d.N = nc; d.K = r;
+    d.A = xt; d.a_rs = r; d.a_cs = 1;
+    d.B = pt + c0; d.b_rs = n; d.b_cs = 1;
+    d.C = ws; d.c_rs1 = 1; d.c_cs1 = m;
+    d.alpha = -1.0; d.beta = 1.0;
+    Timed tm(timer, KC_GEMM, s);
+    if (!ok(launch_copy(ws, Theta + (int64_t)c0 * m, (int64_t)m * nc, s)) || !ok(launch_gemm(d, s))) return out;
+    if (!sumsq(ws, (int64_t)m * nc, b.full + 2 + blocks)) return out;
+  }
+  double res[8], sr = 0.0;
+  if (!ok(hipMemcpyAsync(res, b.full, sizeof(res), hipMemcpyDeviceToHost, s))) return out;
+  if (!ok(hipMemcpyAsync(&sr, b.diag + (r - 1), sizeof(double), hipMemcpyDeviceToHost, s))) return out;
+  if (!sync()) return out;
+  for (int i = 0; i < blocks; ++i) disc += res[2 + i];
+  out.missed = sqrt(res[1] / tot);
+  if (!(out.missed <= 32.0 * kU)) return refuse("not converged", out.missed);
+  // Eq. (eps) again, with the discarded weight as it was summed: the tail at
+  // r - 1 is not below eps of the total, that at r is (unless the cap binds);
+  // and the kept values stand clear of the noise level, below which the rule
+  // keeps none.
+  const double cut = eps * tot, k = std::min(m, n);
+  if (!(sr > 100.0 * 8.0 * sqrt(k) * kU * sqrt(tot))) return refuse("kept values near the noise level", sr);
+  if (r > 1 && !(disc + sr * sr >= cut * (1.0 + 1e-6))) return refuse("the rule is not sure at the rank", disc / tot);
+  if (r < cap && !(disc < cut * (1.0 - 1e-6))) return refuse("the rule is not sure below the cap", disc / tot);
+  out.rank = r;
+  out.disc = disc;
+  out.total = tot;
+  out.filters = filters;
+  if (trace)
+    fprintf(stderr, "[ttm] psvd %dx%d l=%d filters=%d sweeps=%d rank=%d missed=%.2e disc=%.3e total=%.3e\n", m, n, l,
+            filters, out.sweeps, r, out.missed, disc, tot);
   return out;
 }
 

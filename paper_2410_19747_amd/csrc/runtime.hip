@@ -621,6 +621,36 @@ struct Runner {
     return rs.rank;
   }
 
+  // ---- the cap leading triplets of a swap matrix (psvd_oside) with the same
+  // bookkeeping as svd(), which counts them as the full SVD they stand for.
+  // *done = false when it was refused and the full SVD must run.
+  int psvd(const SvdPlan &sp, const double *Y, int cap, double *pt, double *xt, double *ws, bool *done) {
+    *done = false;
+    const int m = sp.np, n = sp.no;
+    PsvdResult ps = psvd_oside(Y, m, n, cap, eps_, o.svd_max_sweeps, pt, xt, ws, st, &timer, trace);
+    jac_sweeps += ps.sweeps;
+    jac_max = std::max(jac_max, ps.sweeps);
+    if (ps.err != TTM_OK) {
+      if (err == TTM_OK) err = ps.err;
+      return -1;
+    }
+    if (ps.fallback) return 0;
+    *done = true;
+    ++n_svd;
+    disc_sum += ps.disc;
+    err_bound += sqrt(std::max(ps.disc, 0.0));
+    if (n_trace < o.trace_cap) {
+      o.rank_trace[n_trace] = ps.rank;
+      o.discard_trace[n_trace] = ps.disc;
+    }
+    ++n_trace;
+    const double mx = std::max(m, n), k = std::min(m, n);
+    const double f = 4.0 * mx * k * k - (4.0 / 3.0) * k * k * k + 4.0 * (mx + k) * k * ps.rank;
+    flops += f;
+    svd_flops += f;
+    return ps.rank;
+  }
+
   // ---- Swap of Fig. 1C: (P, X) -> (X', P') with X' = U_r S_r, P' = V_r^T.
   void swap(Core &P, Core &X, int cap, int pos = 0, int site = 0) {
     step = "a swap";
@@ -678,6 +708,26 @@ struct Runner {
       r = rsvd(Y, m, n, cap, pn, sws, &done);
       if (r < 0) return;
     }
+    bool have_x = false;
+    if (!done && o.svd_mode == TTM_SVD_JACOBI && !o.forced && !o.block_svd && psvd_eligible(m, n, cap)) {
+      r = psvd(sp, Y, cap, pn, xn, sws, &done);
+      if (r < 0) return;
+      have_x = done;
+      if (done && tape) {
+        // the reverse mode needs the other vectors too: the full SVD, with
+        // these r in the place of its own
+        double *other = take();
+        if (!other) return;
+        const SvdResult so = svd_oside(sp, Y, eps_, cap, r, o.svd_max_sweeps, other, SVD_U_T, nullptr, sws, st, &timer,
+                                       trace, &all);
+        give(other);
+        if (so.err != TTM_OK) {
+          if (err == TTM_OK) err = so.err;
+          return;
+        }
+        if (!hip(launch_copy(all.u, pn, (int64_t)n * r, st))) return;
+      }
+    }
     if (!done) r = svd(sp, Y, sws, cap, pn, SVD_U_T, tape ? &all : nullptr);
     if (r < 1) return;
     // X' = Theta V_r = U_r S_r -> [Dl, dx, r]
@@ -686,7 +736,7 @@ struct Runner {
     z.A = Y; z.a_rs = 1; z.a_cs = m;
     z.B = pn; z.b_rs = 1; z.b_cs = n;
     z.C = xn; z.c_rs1 = r; z.c_cs1 = 1;
-    {
+    if (!have_x) {
       Timed tm(&timer, KC_GEMM, st);
       if (!hip(launch_gemm(z, st))) return;
     }

@@ -62,6 +62,72 @@ __global__ void sorted_sigma_kernel(const double *__restrict__ sigma, const int 
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t < n) out[t] = sigma[perm[t]];
 }
+// Jacobi sweeps on b.W until its columns are orthogonal (np, no: the sides
+// of the matrix whose SVD this is, for messages).  False with out.err set on
+// a failure; out.sweeps counts.
+bool jacobi_sweeps(const JacobiPlan &jp, JacobiBufs &b, int max_sweeps, int np, int no, SvdResult &out, hipStream_t s,
+                   KernelTimer *timer, int trace) {
+  auto ok = [&](hipError_t e) {
+    if (e != hipSuccess) {
+      out.err = TTM_EHIP;
+      char what[96];
+      snprintf(what, sizeof(what), "the Jacobi sweeps of a %d x %d matrix", np, no);
+      note_hip_error(e, what);
+      if (trace) fprintf(stderr, "[ttm] HIP error %s (%s) in %s\n", hipGetErrorName(e), hipGetErrorString(e), what);
+      return false;
+    }
+    return true;
+  };
+  auto sync = [&]() {
+    if (!ok(hipStreamSynchronize(s))) return false;
+    if (timer && timer->on) timer->collect();
+    return true;
+  };
+  const double tol = sqrt((double)std::max(jp.L, 1)) * kUnitRoundoff;
+  double prev = INFINITY;
+  bool conv = false;
+  double res[8];
+  for (int sw = 0; sw < max_sweeps; ++sw) {
+    {
+      Timed tm(timer, KC_JAC_OTHER, s);
+      if (!ok(launch_jacobi_sort_columns(jp, b, s))) return false;
+    }
+    if (!ok(launch_jacobi_sweep(jp, b, tol, s, timer))) return false;
+    ++out.sweeps;
+    if (!ok(hipMemcpyAsync(res, b.result, sizeof(res), hipMemcpyDeviceToHost, s))) return false;
+    if (!sync()) return false;
+    const double off = res[3];
+    if (trace >= 2) fprintf(stderr, "[ttm]   jacobi %dx%d sweep %d off=%.3e tol=%.3e\n", jp.L, jp.nc, sw, off, tol);
+    if (!(off == off)) break;  // NaN
+    if (off <= tol) {
+      conv = true;
+      break;
+    }
+    // Cyclic Jacobi converges quadratically at the end: after a sweep whose
+    // largest scaled off-diagonal was off, what remains is of order off^2
+    // (measured here: 3.6e-4 -> 7.9e-9 -> at the tolerance).  Once off^2 is
+    // a hundredth of the tolerance the next sweep's rotations are below the
+    // rounding level, so it is not run.
+    if (off * off <= 0.01 * tol) {
+      conv = true;
+      break;
+    }
+    // stagnation at the rounding floor
+    if (off < 1e3 * tol && off > 0.5 * prev) {
+      conv = true;
+      break;
+    }
+    prev = off;
+  }
+  if (!conv) {
+    out.err = TTM_ENOCONV;
+    set_last_error("one-sided Jacobi on the %d x %d factor of a %d x %d SVD did not converge in %d sweeps",
+                   jp.L, jp.nc, np, no, out.sweeps);
+    if (trace) fprintf(stderr, "[ttm] jacobi %dx%d did not converge\n", jp.L, jp.nc);
+    return false;
+  }
+  return true;
+}
 }  // namespace
 
 SvdPlan svd_plan(int np, int no, int force_bw) {
@@ -235,54 +301,13 @@ SvdResult svd_oside(const SvdPlan &p, const double *Y, double eps, int cap, int 
     if (!ok(launch_rt_from_qr(b.Xt, p.np, p.k, p.k, jp.ncp, b.jb.W, s))) return out;
   }
   // 3. Jacobi sweeps until the columns of W are orthogonal
-  const double tol = sqrt((double)std::max(jp.L, 1)) * kUnitRoundoff;
-  double prev = INFINITY;
-  bool conv = false;
-  double res[8];
-  for (int sw = 0; sw < max_sweeps; ++sw) {
-    {
-      Timed tm(timer, KC_JAC_OTHER, s);
-      if (!ok(launch_jacobi_sort_columns(jp, b.jb, s))) return out;
-    }
-    if (!ok(launch_jacobi_sweep(jp, b.jb, tol, s, timer))) return out;
-    ++out.sweeps;
-    if (!ok(hipMemcpyAsync(res, b.jb.result, sizeof(res), hipMemcpyDeviceToHost, s))) return out;
-    if (!sync()) return out;
-    const double off = res[3];
-    if (trace >= 2) fprintf(stderr, "[ttm]   jacobi %dx%d sweep %d off=%.3e tol=%.3e\n", jp.L, jp.nc, sw, off, tol);
-    if (!(off == off)) break;  // NaN
-    if (off <= tol) {
-      conv = true;
-      break;
-    }
-    // Cyclic Jacobi converges quadratically at the end: after a sweep whose
-    // largest scaled off-diagonal was off, what remains is of order off^2
-    // (measured here: 3.6e-4 -> 7.9e-9 -> at the tolerance).  Once off^2 is
-    // a hundredth of the tolerance the next sweep's rotations are below the
-    // rounding level, so it is not run.
-    if (off * off <= 0.01 * tol) {
-      conv = true;
-      break;
-    }
-    // stagnation at the rounding floor
-    if (off < 1e3 * tol && off > 0.5 * prev) {
-      conv = true;
-      break;
-    }
-    prev = off;
-  }
-  if (!conv) {
-    out.err = TTM_ENOCONV;
-    set_last_error("one-sided Jacobi on the %d x %d factor of a %d x %d SVD did not converge in %d sweeps",
-                   jp.L, jp.nc, p.np, p.no, out.sweeps);
-    if (trace) fprintf(stderr, "[ttm] jacobi %dx%d did not converge\n", jp.L, jp.nc);
-    return out;
-  }
+  if (!jacobi_sweeps(jp, b.jb, max_sweeps, p.np, p.no, out, s, timer, trace)) return out;
   // 4. singular values and the rank rule
   {
     Timed tm(timer, KC_JAC_OTHER, s);
     if (!ok(launch_jacobi_finish(jp, b.jb, eps, cap, forced, s, full_total))) return out;
   }
+  double res[8];
   if (!ok(hipMemcpyAsync(res, b.jb.result, sizeof(res), hipMemcpyDeviceToHost, s))) return out;
   if (!sync()) return out;
   if (res[4] != 0.0) {
@@ -340,6 +365,118 @@ SvdResult svd_oside(const SvdPlan &p, const double *Y, double eps, int cap, int 
   if (trace)
     fprintf(stderr, "[ttm] svd %dx%d sweeps=%d rank=%d disc=%.3e total=%.3e\n", p.np, p.no, out.sweeps,
             out.rank, out.disc, out.total);
+  return out;
+}
+
+int svd_columns_capacity(int n, int l) { return l <= kSvdSmallSide ? l : jacobi_plan(n, l).ncp; }
+
+size_t svd_columns_ws_doubles(int n, int l) {
+  if (l <= kSvdSmallSide)
+    return r32(std::max(qr_inplace_scratch_doubles(n, l), qr_apply_q_scratch_doubles(n, l))) +
+           r32((size_t)((l + kPanel - 1) / kPanel) * kPanel * kPanel) + r32((size_t)l * l) + r32(8);
+  const JacobiPlan jp = jacobi_plan(n, l);
+  return r32((size_t)jp.pairs * jp.gsw * 4 * jp.bw * jp.bw) + r32((size_t)jp.rounds * jp.pairs) +
+         r32((size_t)jp.pairs * 4 * jp.bw * jp.bw) + r32((size_t)jp.pairs) + 2 * r32((size_t)jp.ncp) + r32(8);
+}
+
+SvdResult svd_columns(double *C, double *spare, int n, int l, double eps, int cap, int max_sweeps, double *u,
+                      double *sigma, double *ws, hipStream_t s, KernelTimer *timer, int trace,
+                      const double *full_total) {
+  SvdResult out;
+  double *q = ws;
+  auto adv = [&](size_t nd) {
+    double *x = q;
+    q += r32(nd);
+    return x;
+  };
+  auto ok = [&](hipError_t e) {
+    if (e == hipSuccess) return true;
+    out.err = TTM_EHIP;
+    char what[96];
+    snprintf(what, sizeof(what), "the SVD of %d columns of %d", l, n);
+    note_hip_error(e, what);
+    if (trace) fprintf(stderr, "[ttm] HIP error %s (%s) in %s\n", hipGetErrorName(e), hipGetErrorString(e), what);
+    return false;
+  };
+  auto read = [&](double *res, const double *result) {
+    if (!ok(hipMemcpyAsync(res, result, 8 * sizeof(double), hipMemcpyDeviceToHost, s))) return false;
+    if (!ok(hipStreamSynchronize(s))) return false;
+    if (timer && timer->on) timer->collect();
+    if (res[4] != 0.0) {
+      out.err = TTM_ENONFINITE;
+      set_last_error("the singular values of %d columns of %d are not finite", l, n);
+      return false;
+    }
+    out.rank = (int)res[0];
+    out.disc = res[1];
+    out.total = res[2];
+    return true;
+  };
+  double res[8];
+  if (l <= kSvdSmallSide) {
+    // C = Q1 R, Jacobi on R in one launch, U = Q1 U_R
+    double *qr = adv(std::max(qr_inplace_scratch_doubles(n, l), qr_apply_q_scratch_doubles(n, l)));
+    double *Tall = adv((size_t)((l + kPanel - 1) / kPanel) * kPanel * kPanel);
+    double *uw = adv((size_t)l * l);
+    SvdSmall a;
+    a.result = adv(8);
+    a.mode = SMALL_R;
+    a.src = C; a.ld = n;
+    a.np = l; a.no = n; a.k = l;
+    a.eps = eps; a.cap = cap; a.max_sweeps = max_sweeps;
+    a.full_total = full_total;
+    a.uall = uw; a.uall_ld = l;
+    a.sig = sigma;
+    {
+      Timed tm(timer, KC_QR, s);
+      if (!ok(launch_qr_inplace(C, n, l, qr, nullptr, Tall, s))) return out;
+    }
+    {
+      Timed tm(timer, KC_JAC_SOLVE, s);
+      if (!ok(launch_svd_small(a, s))) return out;
+    }
+    if (!read(res, a.result)) return out;
+    out.sweeps = (int)fabs(res[7]);
+    if (!(res[7] > 0.0)) {
+      out.err = TTM_ENOCONV;
+      set_last_error("one-sided Jacobi on %d columns of %d did not converge in %d sweeps", l, n, out.sweeps);
+      return out;
+    }
+    {
+      Timed tm(timer, KC_JAC_OTHER, s);
+      if (!ok(launch_embed_rows(u, uw, l, n, out.rank, s))) return out;
+    }
+    Timed tm(timer, KC_QR, s);
+    ok(launch_apply_q(C, n, l, Tall, u, out.rank, qr, s));
+    return out;
+  }
+  const JacobiPlan jp = jacobi_plan(n, l);
+  JacobiBufs b;
+  b.W = C;
+  b.Wt = spare;
+  b.part = adv((size_t)jp.pairs * jp.gsw * 4 * jp.bw * jp.bw);
+  b.conv = adv((size_t)jp.rounds * jp.pairs);
+  b.qbuf = adv((size_t)jp.pairs * 4 * jp.bw * jp.bw);
+  b.flag = reinterpret_cast<int *>(adv((size_t)jp.pairs));
+  b.sigma = adv((size_t)jp.ncp);
+  b.perm = reinterpret_cast<int *>(adv((size_t)jp.ncp));
+  b.result = adv(8);
+  {
+    Timed tm(timer, KC_JAC_OTHER, s);
+    if (jp.ncp > l && !ok(launch_fill(C + (int64_t)l * n, 0.0, (int64_t)(jp.ncp - l) * n, s))) return out;
+    if (!ok(launch_column_norms(C, n, jp.ncp, b.sigma, s))) return out;
+    if (!ok(launch_frob_from_norms(b.sigma, jp.ncp, b.result, s))) return out;
+  }
+  if (!jacobi_sweeps(jp, b, max_sweeps, n, l, out, s, timer, trace)) return out;
+  {
+    Timed tm(timer, KC_JAC_OTHER, s);
+    if (!ok(launch_jacobi_finish(jp, b, eps, cap, 0, s, full_total))) return out;
+  }
+  if (!read(res, b.result)) return out;
+  Timed tm(timer, KC_JAC_OTHER, s);
+  if (!ok(launch_jacobi_write_u(jp, b, nullptr, out.rank, u, 1, n, s))) return out;
+  hipLaunchKernelGGL(sorted_sigma_kernel, dim3((l + 255) / 256), dim3(256), 0, s, b.sigma, b.perm, l, sigma);
+  ok(hipGetLastError());
   return out;
 }
 

@@ -182,4 +182,27 @@ int ttm_test_cholqr2(double *Y, int p, int l, int *breakdown, void *ws, size_t w
   return e == hipSuccess ? TTM_OK : TTM_EHIP;
 }
 
+size_t ttm_test_capped_svd_ws_bytes(int m, int n, int cap) {
+  if (m < 1 || n < 1 || cap < 1 || !ttm::psvd_eligible(m, n, cap)) return 0;
+  return ttm::svd_ws_doubles(ttm::svd_plan(m, n)) * sizeof(double);
+}
+
+int ttm_test_capped_svd(const double *Theta, int m, int n, int cap, double eps, double *pt, double *xt, int *rank,
+                        int *refused, double *weights, void *ws, size_t ws_bytes, void *stream) {
+  if (!Theta || !pt || !xt || !rank || !refused || !weights || !ws || !(eps >= 0.0)) return TTM_EINVAL;
+  const size_t need = ttm_test_capped_svd_ws_bytes(m, n, cap);
+  if (need == 0) return TTM_EUNSUPPORTED;
+  if (ws_bytes < need) return TTM_EWORKSPACE;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const ttm::PsvdResult r =
+      ttm::psvd_oside(Theta, m, n, cap, eps, 60, pt, xt, static_cast<double *>(ws), s, nullptr, 0);
+  *rank = r.rank;
+  *refused = r.fallback ? 1 : 0;
+  weights[0] = r.disc;
+  weights[1] = r.total;
+  weights[2] = r.missed;
+  if (r.err != TTM_OK) return r.err;
+  return hipStreamSynchronize(s) == hipSuccess ? TTM_OK : TTM_EHIP;
+}
+
 }  // extern "C"

@@ -267,9 +267,10 @@ struct SvdAll {
 // from Y itself when both sides are at most kSvdSmallSide (SMALL_Y), or from
 // the triangular factor R of a QR whose smaller side is (SMALL_RT: Jacobi on
 // R^T, whose normalised columns are the vectors over R's columns; SMALL_RTQ:
-// QR of R^T = Q2 R2 first, the vectors over R's rows).
+// QR of R^T = Q2 R2 first, the vectors over R's rows; SMALL_R: Jacobi on R
+// itself, the vectors over its rows, for an R near a diagonal matrix).
 constexpr int kSvdSmallSide = 128;
-enum { SMALL_Y = 0, SMALL_RT = 1, SMALL_RTQ = 2 };
+enum { SMALL_Y = 0, SMALL_RT = 1, SMALL_RTQ = 2, SMALL_R = 3 };
 struct SvdSmall {
   int mode = SMALL_Y;
   const double *src = nullptr;  // Y (np x no) or S with R in its upper triangle, column-major
@@ -296,6 +297,19 @@ hipError_t launch_embed_rows(double *dst, const double *src, int k, int no, int 
 SvdResult svd_oside(const SvdPlan &p, const double *Y, double eps, int cap, int forced, int max_sweeps,
                     double *u, int u_layout, double *sigma_out, double *ws, hipStream_t s,
                     KernelTimer *timer, int trace, SvdAll *all = nullptr, const double *full_total = nullptr);
+
+// The SVD of C (n x l, column-major, ld n, n >= l) whose columns are near
+// orthogonal already (a projection on a converged basis), so that no
+// preconditioner is due: the leading left singular vectors by the rule of
+// Eq. (eps) into u (n x r, column-major), the l values, decreasing, into
+// sigma.  C has svd_columns_capacity(n, l) columns, of which those from l on
+// are cleared here; C and spare (as large) are overwritten.  full_total as
+// for svd_oside.
+int svd_columns_capacity(int n, int l);
+size_t svd_columns_ws_doubles(int n, int l);
+SvdResult svd_columns(double *C, double *spare, int n, int l, double eps, int cap, int max_sweeps, double *u,
+                      double *sigma, double *ws, hipStream_t s, KernelTimer *timer, int trace,
+                      const double *full_total);
 
 // Randomized truncated SVD of a swap matrix (rsvd.hip): Theta (m x n,
 // column-major, ld m) ~ X' P' with P' = V_r^T (r x n, row-major, written to
@@ -324,6 +338,23 @@ size_t rsvd_ws_doubles(int m, int n, int cap);
 RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, double accept, int max_sweeps,
                       double eps, int sketch_prec, uint64_t seed, int64_t stream_pos, double *pt, double *ws,
                       hipStream_t s, KernelTimer *timer, int trace);
+
+// The cap leading singular triplets of a swap matrix at full accuracy
+// (rsvd.hip): as svd_oside with u = P' = V_r^T (pt, r x n row-major), and
+// X' = Theta V_r (xt, m x r row-major) besides.  fallback = true (no error)
+// where the result was refused: the caller runs svd_oside in the same
+// workspace, whose size (svd_ws_doubles of the full SVD) is enough here.
+struct PsvdResult {
+  int rank = -1;
+  double disc = 0.0, total = 0.0;
+  double missed = 0.0;  // ||(I - Z Z^T) Theta V_r||_F / ||Theta||_F
+  int sweeps = 0, filters = 0;
+  bool fallback = false;
+  int err = 0;
+};
+bool psvd_eligible(int m, int n, int cap);
+PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
+                      double *ws, hipStream_t s, KernelTimer *timer, int trace);
 
 // ------------------------------------------------------------------ reverse mode
 // The record a TTM product keeps for its reverse mode: one entry per step,
