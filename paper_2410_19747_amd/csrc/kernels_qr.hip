@@ -753,7 +753,7 @@ __device__ __forceinline__ double vload(const double *Vs, int m, int jb, int c, 
 //   rows of one column).
 // When cnorm is not null, cnorm[column] receives the norm of the updated
 // column over rows j0 + next .. m-1 (the next panel's candidates).
-__global__ __launch_bounds__(UNT) void qr_update_kernel(double *S, int m, int j0, int c0, int nc,
+__global__ __launch_bounds__(UNT, 2) void qr_update_kernel(double *S, int m, int j0, int c0, int nc,
                                                         const double *Vs, int jb,
                                                         const double *__restrict__ T, int trans,
                                                         double *__restrict__ cnorm, int next) {
@@ -852,7 +852,7 @@ constexpr int URC = 128;
 
 static inline int update_chunks(int mv) { return (mv + URC - 1) / URC; }
 
-__global__ __launch_bounds__(UNT) void qr_update_part_kernel(const double *S, int m, int j0, int c0, int nc,
+__global__ __launch_bounds__(UNT, 2) void qr_update_part_kernel(const double *S, int m, int j0, int c0, int nc,
                                                              const double *Vs, int jb, double *__restrict__ part) {
   __shared__ double Wp[4][QB][QB + 1];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -882,7 +882,7 @@ __global__ __launch_bounds__(UNT) void qr_update_part_kernel(const double *S, in
       (Wp[0][ti][tj] + Wp[1][ti][tj]) + (Wp[2][ti][tj] + Wp[3][ti][tj]);
 }
 
-__global__ __launch_bounds__(UNT) void qr_update_apply_kernel(double *S, int m, int j0, int c0, int nc,
+__global__ __launch_bounds__(UNT, 2) void qr_update_apply_kernel(double *S, int m, int j0, int c0, int nc,
                                                               const double *Vs, int jb,
                                                               const double *__restrict__ T, int trans,
                                                               const double *__restrict__ part) {
@@ -982,7 +982,7 @@ __global__ __launch_bounds__(UNT) void qr_update_reduce_kernel(const double *__r
 }
 
 template <int K>
-__global__ __launch_bounds__(UNT) void qr_update_apply_w2_kernel(double *S, int m, int j0, int c0, int nc,
+__global__ __launch_bounds__(UNT, 2) void qr_update_apply_w2_kernel(double *S, int m, int j0, int c0, int nc,
                                                                  const double *Vs, int nbw,
                                                                  const double *__restrict__ w2) {
   __shared__ double W2[K][QB + 1];
@@ -1034,7 +1034,7 @@ constexpr int AGG_MIN_ROWS = 4096;
 // grid (chunks).  gpart[ch][t] (t < 6: the cross blocks (p, q), p < q, in
 // the order (0,1) (0,2) (0,3) (1,2) (1,3) (2,3); 16 x 16 row-major) =
 // V_p^T V_q over the chunk's rows; wave w takes tiles w and w + 4.
-__global__ __launch_bounds__(UNT) void qr_vgram_part_kernel(const double *Vs, int m, int mv, int nbw,
+__global__ __launch_bounds__(UNT, 2) void qr_vgram_part_kernel(const double *Vs, int m, int mv, int nbw,
                                                             double *__restrict__ gpart) {
   constexpr int PQ[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -1105,7 +1105,7 @@ __global__ __launch_bounds__(UNT) void qr_tagg_kernel(const double *__restrict__
 // As qr_update_part_kernel with V of AGG columns: part[cb][ch] = V_ch^T A_ch
 // (AGG x 16, row-major).  Wave w reduces URC / 4 rows for all four 16-row
 // tiles of V^T.
-__global__ __launch_bounds__(UNT) void qr_update64_part_kernel(const double *S, int m, int j0, int c0, int nc,
+__global__ __launch_bounds__(UNT, 2) void qr_update64_part_kernel(const double *S, int m, int j0, int c0, int nc,
                                                                const double *Vs, int nbw,
                                                                double *__restrict__ part) {
   __shared__ double Wp[4][AGG][QB + 1];

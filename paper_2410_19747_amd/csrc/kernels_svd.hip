@@ -492,7 +492,7 @@ __device__ int solve_pair(const double *__restrict__ part, int sw, double tol, d
 // with the four 16-column operand blocks of a k-step loaded once for ten
 // products, and the four waves' tiles are summed through LDS at the end.
 template <int BW, int RC>
-__global__ __launch_bounds__(JNT) void jacobi_gram_kernel(const double *__restrict__ W, int L, int nblk, int xs,
+__global__ __launch_bounds__(JNT, 2) void jacobi_gram_kernel(const double *__restrict__ W, int L, int nblk, int xs,
                                                           int round, double *__restrict__ part, int gsw,
                                                           int gsub) {
   __shared__ typename Pair<BW>::template Tile<RC> P;
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(Pair<BW>::THREADS) void jacobi_solve_kernel(int L, 
 // A wave reads all of its rows before it writes them.  A pair that did not
 // rotate stores nothing.
 template <int BW, int RC>
-__global__ __launch_bounds__(JNT) void jacobi_apply_kernel(double *__restrict__ W, int L, int nblk, int xs,
+__global__ __launch_bounds__(JNT, 2) void jacobi_apply_kernel(double *__restrict__ W, int L, int nblk, int xs,
                                                            int round, const double *__restrict__ qbuf,
                                                            const int *__restrict__ flag) {
   constexpr int B2 = Pair<BW>::B2, QPER = B2 * B2 / JNT, KS = B2 / 4, NC = B2 / 16;
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(JNT) void jacobi_apply_kernel(double *__restrict__ 
 // Gram product over those rows.  A pair that did not rotate goes through
 // the identity (exact in FP64).
 template <bool MULTI>
-__global__ __launch_bounds__(JNT) void jacobi_xor_round_kernel(double *__restrict__ W, int L, int round,
+__global__ __launch_bounds__(JNT, 2) void jacobi_xor_round_kernel(double *__restrict__ W, int L, int round,
                                                                const double *__restrict__ qbuf,
                                                                const int *__restrict__ flag,
                                                                double *__restrict__ part, int gsw, int xsub) {
