@@ -100,48 +100,37 @@ __device__ __forceinline__ double rsqrt_nr(double d) {
 // holds the block's diagonal as it was before any elimination (the squared
 // column norms); a pivot at or below 64 u gd_j, or not positive, sets *fail
 // and is replaced by gd_j (or 1) so that everything stays finite.
-// Thread t owns the 4 x 4 tile (t / 16, t % 16) of the block in registers.
-// Factorisation, four rows per step: the sixteen threads of tile row s
-// publish rows 4s .. 4s+3 in LDS (double-buffered), one barrier; every
-// thread factors the 4 x 4 diagonal block U^T U itself, forms the block's
-// rows of R at its tile's four columns and four rows by U^-T, and tiles
-// below and right of the block take the rank-four update; tile row s
-// becomes its rows of R.  Inverse, by block rows from the bottom: the
-// threads of tile row b form X_b = U_bb^-1 (their accumulated right-hand
-// side) and publish it; after one barrier every tile row above subtracts
-// R_a,b X_b from its accumulator.
-__device__ __forceinline__ void inv4_upper(const double (&u)[4][4], double (&x)[4][4]) {
-  const double d0 = 1.0 / u[0][0], d1 = 1.0 / u[1][1], d2 = 1.0 / u[2][2], d3 = 1.0 / u[3][3];
-  x[0][0] = d0; x[1][1] = d1; x[2][2] = d2; x[3][3] = d3;
-  x[1][0] = x[2][0] = x[2][1] = x[3][0] = x[3][1] = x[3][2] = 0.0;
-  x[0][1] = -u[0][1] * d1 * d0;
-  x[1][2] = -u[1][2] * d2 * d1;
-  x[2][3] = -u[2][3] * d3 * d2;
-  x[0][2] = -(u[0][1] * x[1][2] + u[0][2] * d2) * d0;
-  x[1][3] = -(u[1][2] * x[2][3] + u[1][3] * d3) * d1;
-  x[0][3] = -(u[0][1] * x[1][3] + u[0][2] * x[2][3] + u[0][3] * d3) * d0;
-}
-
-__global__ __launch_bounds__(CNT) void chol_diag_kernel(const double *__restrict__ G, int ld, int w,
-                                                        const double *__restrict__ gd, double *__restrict__ rinv,
-                                                        double *__restrict__ rout, int *__restrict__ fail) {
-  static_assert(CNB == 64 && CNT == 256, "one 4 x 4 tile per thread");
-  constexpr int LD = CNB + 2;  // 16-byte aligned rows
-  __shared__ __align__(16) double R[CNB][LD];
-  __shared__ __align__(16) double Xs[CNB][LD];
-  __shared__ __align__(16) double rb[2][4][CNB];
+// Elimination of [G_kk | I] to [R | R^-T]: thread t < 256 owns the 4 x 4 tile
+// (t / 16, t % 16) of the left half in registers, thread 256 + t that of the
+// right.  Four rows per step s: the thread of tile (s, s) publishes it; the
+// threads of tile row s (two waves) factor that block U^T U and turn their
+// rows into rows of [R | R^-T] by U^-T, and publish them; the tiles below take
+// the rank-four update.  Two barriers a step.
+// Bound by the chain of the 64 pivots (a reciprocal root and its Newton steps
+// each) and 32 barriers.  Measured per block: 32 us with the inverse as
+// sixteen further steps after the factorisation; 24 us with it on threads of
+// its own but every thread factoring and solving for itself (issue bound);
+// 23 us in this form.
+__global__ __launch_bounds__(2 * CNT) void chol_diag_kernel(const double *__restrict__ G, int ld, int w,
+                                                            const double *__restrict__ gd, double *__restrict__ rinv,
+                                                            double *__restrict__ rout, int *__restrict__ fail) {
+  static_assert(CNB == 64 && CNT == 256, "one 4 x 4 tile of each half per thread");
+  __shared__ __align__(16) double rows[2][4][2 * CNB];  // four rows of [R | R^-T]
+  __shared__ __align__(16) double pblk[2][4][4];        // the pivot block
   __shared__ double piv[CNB];
   typedef double d2 __attribute__((ext_vector_type(2)));
-  const int t = threadIdx.x, ti = t >> 4, tk = t & 15, i0 = 4 * ti, k0 = 4 * tk;
+  const bool right = threadIdx.x >= CNT;
+  const int t = threadIdx.x & (CNT - 1), ti = t >> 4, tk = t & 15, i0 = 4 * ti, k0 = 4 * tk;
+  const int kc = (right ? CNB : 0) + 2 * tk;
   double a[4][4];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int i = i0 + r, k = k0 + c;
-      a[r][c] = (i < w && k < w) ? G[(int64_t)i * ld + k] : (i == k ? 1.0 : 0.0);
+      a[r][c] = (!right && i < w && k < w) ? G[(int64_t)i * ld + k] : (i == k ? 1.0 : 0.0);
     }
-  if (t < CNB) piv[t] = (t < w) ? gd[t] : 1.0;
+  if (threadIdx.x < CNB) piv[t] = (t < w) ? gd[t] : 1.0;
   bool bad = false;
   auto pivot = [&](double d, double ref, double &r, double &ri) {
     const bool ok = d > 64.0 * kU * ref;  // false for NaN as well
@@ -150,127 +139,86 @@ __global__ __launch_bounds__(CNT) void chol_diag_kernel(const double *__restrict
     ri = rsqrt_nr(d);
     r = d * ri;
   };
-  for (int st = 0; st < CNB / 4; ++st) {
-    const int j0 = 4 * st;
-    double (*buf)[CNB] = rb[st & 1];
-    if (ti == st) {
+  // tile b of a half: its first two columns at 2b, its last two at CNB/2 + 2b,
+  // so that sixteen neighbours read all banks once
+  auto put4 = [&](double (*dst)[2 * CNB], int b) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        *(d2 *)&buf[r][k0] = d2{a[r][0], a[r][1]};
-        *(d2 *)&buf[r][k0 + 2] = d2{a[r][2], a[r][3]};
-      }
+    for (int r = 0; r < 4; ++r) {
+      *(d2 *)&dst[r][b] = d2{a[r][0], a[r][1]};
+      *(d2 *)&dst[r][b + CNB / 2] = d2{a[r][2], a[r][3]};
+    }
+  };
+  auto get4 = [&](double (*src)[2 * CNB], int b, double (&x)[4][4]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const d2 lo = *(const d2 *)&src[r][b], hi = *(const d2 *)&src[r][b + CNB / 2];
+      x[r][0] = lo.x; x[r][1] = lo.y; x[r][2] = hi.x; x[r][3] = hi.y;
+    }
+  };
+#pragma unroll 1
+  for (int st = 0; st < CNB / 4; ++st) {
+    const int j0 = 4 * st, par = st & 1;
+    if (!right && ti == st && tk == st) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) pblk[par][r][c] = a[r][c];
     }
     __syncthreads();
-    // U^T U = the 4 x 4 diagonal block (upper entries of the published rows)
-    double u[4][4], iv[4];
-    pivot(buf[0][j0], piv[j0], u[0][0], iv[0]);
-    u[0][1] = buf[0][j0 + 1] * iv[0];
-    u[0][2] = buf[0][j0 + 2] * iv[0];
-    u[0][3] = buf[0][j0 + 3] * iv[0];
-    pivot(buf[1][j0 + 1] - u[0][1] * u[0][1], piv[j0 + 1], u[1][1], iv[1]);
-    u[1][2] = (buf[1][j0 + 2] - u[0][1] * u[0][2]) * iv[1];
-    u[1][3] = (buf[1][j0 + 3] - u[0][1] * u[0][3]) * iv[1];
-    pivot(buf[2][j0 + 2] - u[0][2] * u[0][2] - u[1][2] * u[1][2], piv[j0 + 2], u[2][2], iv[2]);
-    u[2][3] = (buf[2][j0 + 3] - u[0][2] * u[0][3] - u[1][2] * u[1][3]) * iv[2];
-    pivot(buf[3][j0 + 3] - u[0][3] * u[0][3] - u[1][3] * u[1][3] - u[2][3] * u[2][3], piv[j0 + 3], u[3][3], iv[3]);
-    u[1][0] = u[2][0] = u[2][1] = u[3][0] = u[3][1] = u[3][2] = 0.0;
-    // rows j0 .. j0+3 of R at a column k: x = U^-T g_k (forward substitution)
-    auto solve = [&](int k, double &x0, double &x1, double &x2, double &x3) {
-      const double g0 = buf[0][k], g1 = buf[1][k], g2 = buf[2][k], g3 = buf[3][k];
-      x0 = g0 * iv[0];
-      x1 = (g1 - u[0][1] * x0) * iv[1];
-      x2 = (g2 - u[0][2] * x0 - u[1][2] * x1) * iv[2];
-      x3 = (g3 - u[0][3] * x0 - u[1][3] * x1 - u[2][3] * x2) * iv[3];
-    };
-    double xk[4][4], xi[4][4];  // [block row][own column / own row]
+    if (ti == st) {
+      double p[4][4], u[4][4], iv[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      solve(k0 + c, xk[0][c], xk[1][c], xk[2][c], xk[3][c]);
-      solve(i0 + c, xi[0][c], xi[1][c], xi[2][c], xi[3][c]);
-    }
-    const bool upd = (ti > st) && (tk > st);
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+        for (int c = r; c < 4; ++c) p[r][c] = pblk[par][r][c];
+      pivot(p[0][0], piv[j0], u[0][0], iv[0]);
+#pragma unroll
+      for (int c = 1; c < 4; ++c) u[0][c] = p[0][c] * iv[0];
+      pivot(p[1][1] - u[0][1] * u[0][1], piv[j0 + 1], u[1][1], iv[1]);
+#pragma unroll
+      for (int c = 2; c < 4; ++c) u[1][c] = (p[1][c] - u[0][1] * u[0][c]) * iv[1];
+      pivot(p[2][2] - u[0][2] * u[0][2] - u[1][2] * u[1][2], piv[j0 + 2], u[2][2], iv[2]);
+      u[2][3] = (p[2][3] - u[0][2] * u[0][3] - u[1][2] * u[1][3]) * iv[2];
+      pivot(p[3][3] - u[0][3] * u[0][3] - u[1][3] * u[1][3] - u[2][3] * u[2][3], piv[j0 + 3], u[3][3], iv[3]);
+      // forward substitution of the tile's columns: x = U^-T g
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const double nv = fma(-xi[3][r], xk[3][c], fma(-xi[2][r], xk[2][c],
-                              fma(-xi[1][r], xk[1][c], fma(-xi[0][r], xk[0][c], a[r][c]))));
-        const double rrow = (tk > st) ? xk[r][c] : (tk == st ? u[r][c] : 0.0);
-        a[r][c] = (ti == st) ? rrow : (upd ? nv : a[r][c]);
+        a[0][c] = a[0][c] * iv[0];
+        a[1][c] = (a[1][c] - u[0][1] * a[0][c]) * iv[1];
+        a[2][c] = (a[2][c] - u[0][2] * a[0][c] - u[1][2] * a[1][c]) * iv[2];
+        a[3][c] = (a[3][c] - u[0][3] * a[0][c] - u[1][3] * a[1][c] - u[2][3] * a[2][c]) * iv[3];
       }
-  }
-  if (bad && t == 0) atomicOr(fail, 1);
-  // R (zero below the diagonal tiles) into LDS, and out when asked for
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double z = (ti > tk) ? 0.0 : 1.0;
-    *(d2 *)&R[i0 + r][k0] = d2{a[r][0] * z, a[r][1] * z};
-    *(d2 *)&R[i0 + r][k0 + 2] = d2{a[r][2] * z, a[r][3] * z};
-    if (rout && i0 + r < w) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (k0 + c < w) rout[(int64_t)(i0 + r) * ld + k0 + c] = a[r][c] * z;
-    }
-  }
-  __syncthreads();
-  // R^-1 by block rows from the bottom; acc is this tile's right-hand side.
-  double acc[4][4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = (ti == tk && r == c) ? 1.0 : 0.0;
-  for (int bb = CNB / 4 - 1; bb >= 0; --bb) {
-    if (ti == bb) {
-      double ub[4][4], ui[4][4], xo[4][4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) ub[r][c] = R[4 * bb + r][4 * bb + c];
-      inv4_upper(ub, ui);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          double v = 0.0;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v = fma(ui[r][q], acc[q][c], v);
-          xo[r][c] = (tk >= bb) ? v : 0.0;
-        }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        *(d2 *)&Xs[i0 + r][k0] = d2{xo[r][0], xo[r][1]};
-        *(d2 *)&Xs[i0 + r][k0 + 2] = d2{xo[r][2], xo[r][3]};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = xo[r][c];
-      }
+      put4(rows[par], kc);
     }
     __syncthreads();
-    if (ti < bb) {
-      double rt[4][4], xt[4][4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const d2 r01 = *(const d2 *)&R[i0 + r][4 * bb], r23 = *(const d2 *)&R[i0 + r][4 * bb + 2];
-        rt[r][0] = r01.x; rt[r][1] = r01.y; rt[r][2] = r23.x; rt[r][3] = r23.y;
-        const d2 x01 = *(const d2 *)&Xs[4 * bb + r][k0], x23 = *(const d2 *)&Xs[4 * bb + r][k0 + 2];
-        xt[r][0] = x01.x; xt[r][1] = x01.y; xt[r][2] = x23.x; xt[r][3] = x23.y;
-      }
+    if (ti > st) {
+      double xk[4][4], xi[4][4];  // [published row][own column / own row]
+      get4(rows[par], kc, xk);
+      get4(rows[par], 2 * ti, xi);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          acc[r][c] = fma(-rt[r][3], xt[3][c], fma(-rt[r][2], xt[2][c],
-                          fma(-rt[r][1], xt[1][c], fma(-rt[r][0], xt[0][c], acc[r][c]))));
+          a[r][c] = fma(-xi[3][r], xk[3][c], fma(-xi[2][r], xk[2][c],
+                        fma(-xi[1][r], xk[1][c], fma(-xi[0][r], xk[0][c], a[r][c]))));
     }
   }
+  if (bad) atomicOr(fail, 1);
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) rinv[(i0 + r) * CNB + k0 + c] = (tk >= ti) ? acc[r][c] : 0.0;
+    for (int c = 0; c < 4; ++c) {
+      const int i = i0 + r, k = k0 + c;
+      if (right)  // entry (i, k) of R^-T
+        rinv[k * CNB + i] = (k <= i) ? a[r][c] : 0.0;
+      else if (rout && i < w && k < w)
+        rout[(int64_t)i * ld + k] = (k >= i) ? a[r][c] : 0.0;
+    }
 }
 
 hipError_t launch_chol_diag(const double *G, int ld, int w, const double *gd, double *rinv, double *rout,
                             int *fail, hipStream_t s) {
-  hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(CNT), 0, s, G, ld, w, gd, rinv, rout, fail);
+  hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(2 * CNT), 0, s, G, ld, w, gd, rinv, rout, fail);
   return hipGetLastError();
 }
 
