@@ -29,16 +29,23 @@
 //    took 1230, 1590 and 2830 cycles per step at 32, 64 and 128 columns,
 //    against 780, 1150 and 1910.
 // Measured, a k x k matrix with values i^-2, whole SVD with its read-back, by
-// the block method and here: k = 8: 486 and 75 us, 16: 570 and 90, 32: 695 and
-// 167, 64: 1026 and 429, 96: 1527 and 1271, 128: 2094 and 1428; 64 x 512: 1100
-// and 585, 1024 x 128: 2151 and 1472.  Above 128 columns the tile no longer
+// the block method and here: k = 8: 446 and 71 us, 16: 522 and 79, 32: 646 and
+// 146, 64: 988 and 367, 96: 1476 and 1223, 128: 2168 and 1261; 64 x 512: 1065
+// and 524, 1024 x 128: 2162 and 1368.  Of it the QR takes 680, 1490, 2150 and
+// 3500 cycles a column and a sweep 10.9, 27, 77 and 261 thousand at 16, 32, 64
+// and 128 columns (with each sum of a QR step read from LDS behind the store
+// of the one before, and the order counted by one thread a column: 860, 1900,
+// 3050 and 4150; 12.1, 29, 81 and 275).  Above 128 columns the tile no longer
 // fits the registers and LDS of one workgroup.
+#include <limits.h>
 #include <math.h>
 
 #include "ttm_internal.h"
 
 namespace ttm {
 namespace {
+typedef double d2 __attribute__((ext_vector_type(2)));
+
 template <int LN, int NW>
 struct SmallTile {
   static constexpr int H = 64 / LN;   // lanes of a wave that share a unit pair
@@ -53,10 +60,11 @@ template <int LN, int NW>
 struct SmallSmem {
   typedef SmallTile<LN, NW> T;
   double W[T::N * T::LD];       // columns of the matrix, staged
-  double part[2][NW][T::N];     // per-wave sums of the columns (or of the pairs), double-buffered
-  double row[2][T::N];          // the pivot row of a QR step
+  __align__(16) double part[2][NW][T::N];  // per-wave sums of the columns (or of the pairs), double-buffered
+  __align__(16) double row[2][T::N];       // the pivot row of a QR step
   double v[NW][T::H][T::RL];    // the pivot column of a QR step, per wave
-  double norm[T::N];            // squared column norms, then the sorted ones
+  __align__(16) double norm[T::N];         // squared column norms, then the sorted ones
+  unsigned count[NW][LN];       // places of four columns, by wave
   int perm[T::N];               // position -> column
   int orow[T::N];               // row of U that each row of W belongs to
   int spos[T::N];               // column -> place among the sorted singular values
@@ -165,60 +173,155 @@ struct Small {
     if (NW == 4) t = (t + sm.part[par][1][c]) + (sm.part[par][2][c] + sm.part[par][3][c]);
     return t;
   }
+  static __device__ __forceinline__ void get4(const double *src, double (&x)[4]) {
+    const d2 lo = *(const d2 *)src, hi = *(const d2 *)(src + 2);
+    x[0] = lo.x; x[1] = lo.y; x[2] = hi.x; x[3] = hi.y;
+  }
+  static __device__ __forceinline__ void put4(double *dst, const double (&x)[4]) {
+    *(d2 *)dst = d2{x[0], x[1]};
+    *(d2 *)(dst + 2) = d2{x[2], x[3]};
+  }
+  // wave_total of the lane's columns.
+  __device__ __forceinline__ void lane_totals(int par, double (&t)[4]) const {
+    double p[NW][4];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) get4(&sm.part[par][i][4 * u], p[i]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = NW == 4 ? (p[0][e] + p[1][e]) + (p[2 % NW][e] + p[3 % NW][e]) : p[0][e];
+  }
   // sm.norm = the squared norms of the columns by slot.
   __device__ __forceinline__ void norms() {
     static_assert(NW == 1 || NW == 4, "wave_total");
     __syncthreads();  // part may still be read
+    double n[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      double a = 0.0;
+#pragma unroll
+      for (int i = 0; i < T::RL; ++i) a = fma(x[e][i], x[e][i], a);
+      n[e] = group_sum<LN>(a);
+    }
+    if (h == 0) put4(NW > 1 ? &sm.part[0][w][4 * u] : &sm.norm[4 * u], n);
+    __syncthreads();
+    if (NW > 1) {
+      if (threadIdx.x < T::N) sm.norm[threadIdx.x] = wave_total(0, threadIdx.x);
+      __syncthreads();
+    }
+  }
+  // sm.perm = the slots by decreasing norm (ties by slot).  Row group q
+  // counts, for the lane's four columns, the norms of slots i Q + q before
+  // them; a column's place is the sum over the groups (at most 127, four
+  // columns to a word).
+  __device__ __forceinline__ void order() {
+    double me[4], o[T::RL];
+    get4(&sm.norm[4 * u], me);
+#pragma unroll
+    for (int i = 0; i < T::RL; ++i) o[i] = sm.norm[i * T::Q + q];
+    unsigned pos = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      unsigned cnt = 0;
+#pragma unroll
+      for (int i = 0; i < T::RL; ++i)
+        cnt += (unsigned)((o[i] > me[e]) | ((o[i] == me[e]) & (i * T::Q + q < 4 * u + e)));
+      pos |= cnt << (8 * e);
+    }
+    if (LN <= 4) pos += __builtin_amdgcn_update_dpp(pos, pos, 0x124, 0xf, 0xf, false);  // row_ror:4
+    if (LN <= 8) pos += __builtin_amdgcn_update_dpp(pos, pos, 0x128, 0xf, 0xf, false);  // row_ror:8
+    if (LN <= 16) {
+      const auto k = __builtin_amdgcn_permlane16_swap(pos, pos, false, false);
+      pos = k[0] + k[1];
+    }
+    const auto k = __builtin_amdgcn_permlane32_swap(pos, pos, false, false);
+    pos = k[0] + k[1];
+    if (NW > 1) {
+      if (h == 0) sm.count[w][u] = pos;
+      if (threadIdx.x < T::N) sm.perm[threadIdx.x] = threadIdx.x;  // every entry a slot, also when a norm is NaN
+      __syncthreads();
+      pos = 0;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) pos += sm.count[i][u];
+    } else {
+      if (threadIdx.x < T::N) sm.perm[threadIdx.x] = threadIdx.x;
+      __syncthreads();
+    }
+    if (w == 0 && h == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sm.perm[(pos >> (8 * e)) & 255] = 4 * u + e;
+    }
+    __syncthreads();
+  }
+
+  // The column of largest remaining norm (left: those norms by lane, negative
+  // for a column that is no candidate), the same in every lane: the maximum
+  // of the norms' high words with the column in their low bits, which leaves
+  // at least 13 bits of the mantissa.
+  __device__ __forceinline__ int pivot_column(const double (&left)[4]) {
+    static_assert(T::N <= 128, "bits of the key");
+    int key = INT_MIN;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key = max(key, (__double2hiint(left[e]) & ~(T::N - 1)) | (4 * u + e));
+    key = max(key, __builtin_amdgcn_update_dpp(key, key, 0xB1, 0xf, 0xf, false));   // quad_perm 1 0 3 2
+    key = max(key, __builtin_amdgcn_update_dpp(key, key, 0x4E, 0xf, 0xf, false));   // quad_perm 2 3 0 1
+    if (LN >= 8) key = max(key, __builtin_amdgcn_update_dpp(key, key, 0x141, 0xf, 0xf, false));   // row_half_mirror
+    if (LN >= 16) key = max(key, __builtin_amdgcn_update_dpp(key, key, 0x140, 0xf, 0xf, false));  // row_mirror
+    if (LN >= 32) {
+      const auto k2 = __builtin_amdgcn_permlane16_swap(key, key, false, false);
+      key = max((int)k2[0], (int)k2[1]);
+    }
+    return __builtin_amdgcn_readfirstlane(key) & (T::N - 1);
+  }
+  // left = the squared norms of what remains of the candidates.
+  __device__ __forceinline__ void remaining(double (&left)[4]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       double a = 0.0;
 #pragma unroll
       for (int i = 0; i < T::RL; ++i) a = fma(x[e][i], x[e][i], a);
       a = group_sum<LN>(a);
-      if (h == 0) sm.part[0][w][4 * u + e] = a;
-    }
-    __syncthreads();
-    if (threadIdx.x < T::N) sm.norm[threadIdx.x] = wave_total(0, threadIdx.x);
-    __syncthreads();
-  }
-  // sm.perm = the slots by decreasing norm (ties by slot).
-  __device__ __forceinline__ void order() {
-    const int c = threadIdx.x;
-    int pos = c;
-    if (c < T::N) {
-      const double me = sm.norm[c];
-      pos = 0;
-#pragma unroll 4
-      for (int j = 0; j < T::N; ++j) {
-        const double o = sm.norm[j];
-        pos += (int)((o > me) | ((o == me) & (j < c)));
+      if (NW > 1) {
+        if (h == 0) sm.part[0][w][4 * u + e] = a;
+      } else {
+        left[e] = left[e] < 0.0 ? left[e] : a;
       }
-      sm.perm[c] = c;  // every entry a slot, also when a norm is NaN
     }
-    __syncthreads();
-    if (c < T::N) sm.perm[pos] = c;
-    __syncthreads();
+    if (NW > 1) {
+      __syncthreads();
+      double a[4];
+      lane_totals(0, a);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) left[e] = left[e] < 0.0 ? left[e] : a[e];
+      __syncthreads();
+    }
   }
 
-  // Householder QR of the tile (kk reflectors): leaves R^T staged, column j
-  // of sm.W = row j of R, columns beyond kk zero.  Finished rows are zeroed
-  // in the registers, so a step's dot products run over whole columns: with
-  // x the pivot column from row j on, s = x^T x, alpha = x_j, beta =
-  // -sign(alpha) sqrt(s) and v = x - beta e_j, every column c loses
-  // v (x^T c - beta c_j) / (s - alpha beta).
+  // Householder QR of the tile with column pivoting (kk reflectors on the
+  // first nc columns; the others are zero): leaves (R P^T)^T staged, column j
+  // of sm.W = row j of R over the columns in their own slots, columns beyond
+  // kk zero.  Finished rows are zeroed in the registers, so a step's dot
+  // products run over whole columns: with x the pivot column from row j on,
+  // s = x^T x, alpha = x_j, beta = -sign(alpha) sqrt(s) and v = x - beta e_j,
+  // every unfinished column c loses v (x^T c - beta c_j) / (s - alpha beta).
+  // The remaining norms lose the square of their entry in row j and are
+  // formed anew every eight steps; they choose the pivot and nothing else.
+  // With the columns only sorted once, Jacobi took 8.4 sweeps on average on
+  // the swaps of a product of bond 32 over 18 modes of 2 and 9.6 on those of
+  // a 64 x 64 field at bond 32; pivoted, 6.5 and 6.3.
   // qr_rows<I> reduces the rows of slot I, so that every register index is
   // known when it is compiled (one loop body with the slots shifted down
   // between row blocks took 1.2 to 1.4 times as long at 64 and 128 columns).
   template <int I>
-  __device__ __forceinline__ void qr_rows(int kk) {
+  __device__ __forceinline__ void qr_rows(int kk, double (&left)[4]) {
     if constexpr (I < T::RL) {
 #pragma unroll 1
       for (int qq = 0; qq < T::Q; ++qq) {
         const int j = I * T::Q + qq;
         if (j >= kk) return;
-        const int par = qq & 1, je = j & 3;
+        if ((j & 7) == 0) remaining(left);
+        const int pc = pivot_column(left);
+        const int par = qq & 1, je = pc & 3;
         const bool mine = (q == qq);
-        if (u == (j >> 2)) {
+        if (u == (pc >> 2)) {
 #pragma unroll
           for (int i = I; i < T::RL; ++i) {
             const double lo = (je & 1) ? x[1][i] : x[0][i], hi = (je & 1) ? x[3][i] : x[2][i];
@@ -226,8 +329,10 @@ struct Small {
           }
         }
         if (mine) {
+          double rc0[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sm.row[par][4 * u + e] = x[e][I];
+          for (int e = 0; e < 4; ++e) rc0[e] = x[e][I];
+          put4(&sm.row[par][4 * u], rc0);
         }
         wave_sync();
         double vv[T::RL], d[4] = {0.0, 0.0, 0.0, 0.0};
@@ -246,22 +351,26 @@ struct Small {
           sm.part[par][w][4 * u + 2 + (lane >> 5)] = d[2];
         }
         __syncthreads();
-        const double s = wave_total(par, j), alpha = sm.row[par][j];
+        // all LDS reads of the step at once
+        const double s = wave_total(par, pc), alpha = sm.row[par][pc];
+        double tot[4], rj[4], f[4], rc[4];
+        lane_totals(par, tot);
+        get4(&sm.row[par][4 * u], rj);
         // The matrix has norm one, so a column with s below 2^-960 (rounding
         // errors of rounding errors, where the matrix has lost its rank) is
         // zero: no reflection, and 1 / s cannot overflow.
         const bool some = s > 0x1p-960;
-        const double sn = some ? s : 1.0;
-        const double beta = some ? -copysign(sn * rsqrt2(sn), alpha) : 0.0;
-        const double inv = some ? recip2(sn - alpha * beta) : 0.0, vj = alpha - beta;  // alpha beta <= 0
-        double f[4];
+        const double sn = some ? s : 1.0, root = sn * rsqrt2(sn);
+        const double beta = some ? -copysign(root, alpha) : 0.0;
+        const double rec = recip2(fma(fabs(alpha), root, sn)), inv = some ? rec : 0.0;
+        const double vj = alpha - beta;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int c = 4 * u + e;
-          const double rj = sm.row[par][c];
-          const double ff = (wave_total(par, c) - beta * rj) * inv;
-          f[e] = (c > j) ? ff : 0.0;
-          if (mine) sm.W[j * T::LD + c] = (c > j) ? fma(-ff, vj, rj) : (c == j ? beta : 0.0);
+          const double ff = (tot[e] - beta * rj[e]) * inv;
+          const bool piv = 4 * u + e == pc, open = left[e] >= 0.0 && !piv;
+          rc[e] = open ? fma(-ff, vj, rj[e]) : (piv ? beta : 0.0);
+          f[e] = open ? ff : 0.0;
+          left[e] = open ? fmax(fma(-rc[e], rc[e], left[e]), 0.0) : -1.0;
         }
 #pragma unroll
         for (int i = I; i < T::RL; ++i)
@@ -269,13 +378,20 @@ struct Small {
           for (int e = 0; e < 4; ++e) x[e][i] = fma(-f[e], vv[i], x[e][i]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e][I] = mine ? 0.0 : x[e][I];
+        if (mine) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sm.W[j * T::LD + 4 * u + e] = rc[e];
+        }
       }
-      qr_rows<I + 1>(kk);
+      qr_rows<I + 1>(kk, left);
     }
   }
-  __device__ __forceinline__ void qr(int kk) {
+  __device__ __forceinline__ void qr(int kk, int nc) {
+    double left[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) left[e] = (4 * u + e < nc) ? 0.0 : -1.0;
     __syncthreads();  // the staged matrix has been fetched
-    qr_rows<0>(kk);
+    qr_rows<0>(kk, left);
     __syncthreads();
 #pragma unroll 1
     for (int e = threadIdx.x; e < (T::N - kk) * T::N; e += T::NT) sm.W[(kk + e / T::N) * T::LD + e % T::N] = 0.0;
@@ -453,7 +569,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
   while (true) {
     s.fetch();
     if ((MODE == SMALL_Y || MODE == SMALL_RTQ) && todo == QR) {
-      s.qr(a.k);
+      s.qr(a.k, MODE == SMALL_Y ? a.no : a.k);
       if (tid < T::N) sm.perm[tid] = tid;
       __syncthreads();
       todo = SORT;

@@ -136,8 +136,8 @@ SvdPlan svd_plan(int np, int no, int force_bw) {
   p.no = no;
   p.k = std::min(np, no);
   // One workgroup up to 128 columns, the most that its tile holds: faster
-  // than the block path below at every size measured (64 x 64: 429 against
-  // 1026 us, 128 x 128: 1428 against 2094, see kernels_svd_small.hip).
+  // than the block path below at every size measured (64 x 64: 367 against
+  // 988 us, 128 x 128: 1261 against 2168, see kernels_svd_small.hip).
   p.small = force_bw == 0 && p.k <= kSvdSmallSide;
   p.jp = jacobi_plan(p.k, p.k, force_bw);
   return p;
