@@ -169,9 +169,10 @@ struct Pair {
   static constexpr int B2 = 2 * BW;    // columns of the pair
   static constexpr int SNT = BW * BW;  // solve threads that own a 2 x 2 block of the Gram
   // 32-column pairs add SNT threads that accumulate the rotation in
-  // registers (see solve_pair); 64-column pairs keep it in LDS.
+  // registers and a wave that computes the rotations a step ahead (see
+  // solve_pair); 64-column pairs keep the accumulated rotation in LDS.
   static constexpr bool QREG = (BW == 16);
-  static constexpr int THREADS = QREG ? 2 * SNT : SNT;
+  static constexpr int THREADS = QREG ? 2 * SNT + 64 : SNT;
   template <int RC>
   using Tile = double[RC][B2 + 1];  // one row chunk of the pair, zero beyond L
   typedef double Square[B2][B2 + 1];
@@ -288,6 +289,28 @@ __device__ __forceinline__ int slot_next(int a, int n) {
   return (a & 1) ? a + 2 : a - 2;
 }
 
+// The slot whose index moves to slot a (the inverse of slot_next).
+__device__ __forceinline__ int slot_prev(int a, int n) {
+  if (a == 1) return 1;
+  if (a == 3) return 0;
+  if (a == n - 2) return n - 1;
+  return (a & 1) ? a - 2 : a + 2;
+}
+
+// A 2 x 2 block (a: its upper row, b: its lower row) after its rows' rotation
+// J_u^T and its columns' J_v.  Written out so that the wave that works a step
+// ahead (rotated_entry in solve_pair) gets bitwise the same entries.
+typedef double d2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void rotate_block(d2v a, d2v b, d2v ru, d2v rv, double (&o)[2][2]) {
+  const double cu = ru.x, su = ru.y, cv = rv.x, sv = rv.y;
+  const double h00 = fma(cu, a.x, -su * b.x), h01 = fma(cu, a.y, -su * b.y);
+  const double h10 = fma(su, a.x, cu * b.x), h11 = fma(su, a.y, cu * b.y);
+  o[0][0] = fma(cv, h00, -sv * h01);
+  o[0][1] = fma(sv, h00, cv * h01);
+  o[1][0] = fma(cv, h10, -sv * h11);
+  o[1][1] = fma(sv, h10, cv * h11);
+}
+
 // Shared memory of the block-pair solve: G and the accumulated rotation Q
 // double-buffered (a step reads one copy and writes the other at permuted
 // positions), rows padded to keep 16-byte alignment for paired loads.
@@ -297,7 +320,7 @@ struct SolveSmem {
   double Gb[2][2 * BW][LD];
   double Qb[2][2 * BW][LD];
   double redmax[BW * BW / 64];
-  double cs[BW][2];  // rotations of the current step
+  double cs[2][BW][2];  // rotations of the current step, and of the next
 };
 
 // Solve of one block pair by its workgroup (BW * BW threads): reduce the sw
@@ -367,36 +390,64 @@ __device__ int solve_pair(const double *__restrict__ part, int sw, double tol, d
 
   // One cyclic sweep of two-sided Jacobi over the B2 indices (B2 - 1 steps),
   // slots (2k, 2k + 1) paired at every step (see slot_next).  Gram thread
-  // (u, v) owns the 2 x 2 block of G at slot pairs (u, v).  Per step: every
-  // Gram thread loads its block while threads 0 .. BW-1 compute the step's
-  // rotations into LDS; after one barrier each applies J_u^T (.) J_v to its
-  // block and writes it to the other buffer at the slots of the next step.
-  // The accumulated rotation Q (rows: the pair's columns, columns: slots):
+  // (u, v) owns the 2 x 2 block of G at slot pairs (u, v): per step it applies
+  // J_u^T (.) J_v to its block and writes it to the other buffer at the slots
+  // of the next step.  The accumulated rotation Q (rows: the pair's columns,
+  // columns: slots):
   //  * 32-column pairs: thread SNT + 8 i + t holds Q(i, 4t .. 4t+3) in
-  //    registers, applies the step's rotations of slot pairs 2t, 2t + 1 after
-  //    the same barrier and moves its values to the next step's slots with
-  //    two row shifts (slot_next moves one slot a lane down, one a lane up);
-  //    it adds no LDS traffic to the Gram threads' critical path;
+  //    registers, applies the step's rotations of slot pairs 2t, 2t + 1 and
+  //    moves its values to the next step's slots with two row shifts
+  //    (slot_next moves one slot a lane down, one a lane up); it adds no LDS
+  //    traffic to the Gram threads' critical path;
   //  * 64-column pairs: Gram thread (u, v) also owns rows 2u, 2u + 1 of Q at
   //    slot pair v, double-buffered in LDS like G.
+  // What bounds a step is its chain: read, rotation, LDS, apply, LDS.  With
+  // 32-column pairs a wave of its own works a step ahead: from this step's G
+  // and rotations its lane k forms the three entries of G that the next
+  // step's pair k needs and their rotation, while the Gram threads apply this
+  // step's, so that a step holds one barrier and the rotation and the
+  // application run side by side: 1180 -> 1000 cycles a step, 17.3 -> 15.7 us
+  // a solve with 16 row chunks (of a step the wave ahead spends about 190 on
+  // its LDS reads, 180 on the entries, 310 on the rotation and 120 at the
+  // barrier; its priority and the order of its reads made no difference; with
+  // all three entries formed by one lane each it took 1340).  With 64-column pairs
+  // (1024 Gram threads, no room for that wave) threads 0 .. BW-1 compute the
+  // step's rotations into LDS before a barrier of their own.
   typedef double d2 __attribute__((ext_vector_type(2)));
   const int u = tid / BW, v = tid % BW;
   const int nu0 = slot_next(2 * u, B2), nu1 = slot_next(2 * u + 1, B2);
   const int nv0 = slot_next(2 * v, B2), nv1 = slot_next(2 * v + 1, B2);
   const int qi = (tid - SNT) >> 3, qt = (tid - SNT) & 7;  // register-Q row and slot quad
+  const bool qthread = Pair<BW>::QREG && !gt && tid < 2 * SNT;
   double q0 = 0.0, q1 = 0.0, q2 = 0.0, q3 = 0.0;
-  if (Pair<BW>::QREG && !gt) {
+  if (qthread) {
     q0 = (qi == 4 * qt) ? 1.0 : 0.0;
     q1 = (qi == 4 * qt + 1) ? 1.0 : 0.0;
     q2 = (qi == 4 * qt + 2) ? 1.0 : 0.0;
     q3 = (qi == 4 * qt + 3) ? 1.0 : 0.0;
   }
-  int cur = 0;
-  for (int step = 0; step < B2 - 1; ++step) {
+  // The wave ahead: lanes k, 16 + k, 32 + k form the entries (p, p), (q, q)
+  // and (p, q) of the next step's pair k = (p, q), at (row, col) of this step.
+  const int rk = lane & 15;
+  const int pa = slot_prev(2 * rk, B2), pb = slot_prev(2 * rk + 1, B2);
+  const int row = (lane >> 4) == 1 ? pb : pa, col = (lane >> 4) == 0 ? pa : pb;
+  const double rsgn = (row & 1) ? 1.0 : -1.0, csgn = (col & 1) ? 1.0 : -1.0;
+  auto rotation = [&](int par, int k, double gpp, double gqq, double gpq) {
+    double c, sn;
+    rot_params(gpp, gqq, gpq, thr, tol2, floor2, c, sn);
+    *(d2 *)&sm.cs[par][k][0] = d2{c, sn};
+  };
+  if (Pair<BW>::QREG) {
+    if (tid >= 2 * SNT && lane < BW)
+      rotation(0, rk, sm.Gb[0][2 * rk][2 * rk], sm.Gb[0][2 * rk + 1][2 * rk + 1], sm.Gb[0][2 * rk][2 * rk + 1]);
+    __syncthreads();
+  }
+  auto one_step = [&](int cur) {
     double (*Gc)[SolveSmem<BW>::LD] = sm.Gb[cur];
     double (*Gn)[SolveSmem<BW>::LD] = sm.Gb[cur ^ 1];
     double (*Qc)[SolveSmem<BW>::LD] = sm.Qb[cur];
     double (*Qn)[SolveSmem<BW>::LD] = sm.Qb[cur ^ 1];
+    const int par = Pair<BW>::QREG ? cur : 0;
     d2 ga = {0.0, 0.0}, gb = {0.0, 0.0}, qa = {0.0, 0.0}, qb = {0.0, 0.0};
     if (gt) {
       ga = *(const d2 *)&Gc[2 * u][2 * v];
@@ -406,32 +457,30 @@ __device__ int solve_pair(const double *__restrict__ part, int sw, double tol, d
         qb = *(const d2 *)&Qc[2 * u + 1][2 * v];
       }
     }
-    if (tid < BW) {
-      const d2 dg = *(const d2 *)&Gc[2 * tid][2 * tid];
-      double c, sn;
-      rot_params(dg.x, Gc[2 * tid + 1][2 * tid + 1], dg.y, thr, tol2, floor2, c, sn);
-      const d2 cs = {c, sn};
-      *(d2 *)&sm.cs[tid][0] = cs;
+    if (!Pair<BW>::QREG) {
+      if (tid < BW) {
+        const d2 dg = *(const d2 *)&Gc[2 * tid][2 * tid];
+        rotation(0, tid, dg.x, Gc[2 * tid + 1][2 * tid + 1], dg.y);
+      }
+      __syncthreads();
     }
-    __syncthreads();
     if (gt) {
-      const d2 ru = *(const d2 *)&sm.cs[u][0], rv = *(const d2 *)&sm.cs[v][0];
-      const double cu = ru.x, su = ru.y, cv = rv.x, sv = rv.y;
-      // rows (J_u^T), then columns (J_v)
-      const double h00 = cu * ga.x - su * gb.x, h01 = cu * ga.y - su * gb.y;
-      const double h10 = su * ga.x + cu * gb.x, h11 = su * ga.y + cu * gb.y;
-      Gn[nu0][nv0] = cv * h00 - sv * h01;
-      Gn[nu0][nv1] = sv * h00 + cv * h01;
-      Gn[nu1][nv0] = cv * h10 - sv * h11;
-      Gn[nu1][nv1] = sv * h10 + cv * h11;
+      const d2 ru = *(const d2 *)&sm.cs[par][u][0], rv = *(const d2 *)&sm.cs[par][v][0];
+      double o[2][2];
+      rotate_block(ga, gb, ru, rv, o);
+      Gn[nu0][nv0] = o[0][0];
+      Gn[nu0][nv1] = o[0][1];
+      Gn[nu1][nv0] = o[1][0];
+      Gn[nu1][nv1] = o[1][1];
       if (!Pair<BW>::QREG) {
+        const double cv = rv.x, sv = rv.y;
         Qn[2 * u][nv0] = cv * qa.x - sv * qa.y;
         Qn[2 * u][nv1] = sv * qa.x + cv * qa.y;
         Qn[2 * u + 1][nv0] = cv * qb.x - sv * qb.y;
         Qn[2 * u + 1][nv1] = sv * qb.x + cv * qb.y;
       }
-    } else if (Pair<BW>::QREG) {
-      const d2 r0 = *(const d2 *)&sm.cs[2 * qt][0], r1 = *(const d2 *)&sm.cs[2 * qt + 1][0];
+    } else if (qthread) {
+      const d2 r0 = *(const d2 *)&sm.cs[par][2 * qt][0], r1 = *(const d2 *)&sm.cs[par][2 * qt + 1][0];
       const double n0 = r0.x * q0 - r0.y * q1, n1 = r0.y * q0 + r0.x * q1;
       const double n2 = r1.x * q2 - r1.y * q3, n3 = r1.y * q2 + r1.x * q3;
       // Slot 4t + 3 of the lane below moves to slot 4t + 1 here, slot 4t of
@@ -443,16 +492,39 @@ __device__ int solve_pair(const double *__restrict__ part, int sw, double tol, d
       q1 = (qt == 0) ? n1 : from_below;
       q2 = (qt == 7) ? n3 : from_above;
       q3 = (qt == 0) ? n0 : n1;
+    } else if (Pair<BW>::QREG) {
+      // rotated_entry: rotate_block's entry (row & 1, col & 1), the first
+      // factors picked by address, the sign of the second by rsgn, csgn
+      const int bu = row >> 1, bv = col >> 1;
+      const d2 a = *(const d2 *)&Gc[2 * bu][2 * bv], b = *(const d2 *)&Gc[2 * bu + 1][2 * bv];
+      const double m1 = sm.cs[par][bu][row & 1], m2 = sm.cs[par][bu][~row & 1] * rsgn;
+      const double n1 = sm.cs[par][bv][col & 1], n2 = sm.cs[par][bv][~col & 1] * csgn;
+      const double h0 = fma(m1, a.x, m2 * b.x), h1 = fma(m1, a.y, m2 * b.y);
+      const double g = fma(n1, h0, n2 * h1);
+      const int lo = __double2loint(g), hi = __double2hiint(g);
+      const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);  // [1]: lane 16 + k
+      const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+      const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);  // [1]: lane 32 + k
+      const auto h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+      if (lane < BW)
+        rotation(par ^ 1, rk, g, __hiloint2double(h16[1], l16[1]), __hiloint2double(h32[1], l32[1]));
     }
-    cur ^= 1;
     __syncthreads();
+  };
+  // two steps to a round of the loop, so that the buffers' addresses are fixed
+#pragma unroll 1
+  for (int step = 0; step < B2 - 2; step += 2) {
+    one_step(0);
+    one_step(1);
   }
+  one_step(0);
+  const int cur = 1;  // B2 - 1 steps, an odd number
   // B2 - 1 steps have returned every index to its own slot: Q is in index
   // order.  G is no longer needed; its other buffer holds Q^T Q below.
   double (*Qf)[SolveSmem<BW>::LD] = Pair<BW>::QREG ? sm.Qb[0] : sm.Qb[cur];
   double (*Sq)[SolveSmem<BW>::LD] = sm.Gb[0];
   if (Pair<BW>::QREG) {
-    if (!gt) {
+    if (qthread) {
       const d2 a = {q0, q1}, b = {q2, q3};
       *(d2 *)&Qf[qi][4 * qt] = a;
       *(d2 *)&Qf[qi][4 * qt + 2] = b;
