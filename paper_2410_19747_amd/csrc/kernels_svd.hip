@@ -990,6 +990,31 @@ hipError_t launch_jacobi_sweep(const JacobiPlan &p, const JacobiBufs &b, double 
   return hipGetLastError();
 }
 
+hipError_t launch_jacobi_neighbours(const JacobiPlan &p, const JacobiBufs &b, int passes, double tol, hipStream_t s,
+                                    KernelTimer *timer) {
+  const double ns = 8.0 * sqrt((double)p.L) * 2.220446049250313e-16;
+  if (p.bw != 16 && p.bw != 32) return hipErrorInvalidValue;
+  for (int i = 0; i < 2 * passes; ++i) {
+    // round 0 of the XOR pairing, over all blocks and then over all but the ends
+    JacobiPlan q = p;
+    JacobiBufs c = b;
+    q.xs = 1;
+    if (i & 1) {
+      if (p.nblk <= 2) continue;
+      q.nblk -= 2;
+      q.pairs -= 1;
+      c.W += (int64_t)p.bw * p.L;
+    }
+    if (p.bw == 32)
+      launch_round<32, ROWS_PER_WG>(q, c, 0, tol, ns * ns, s, timer, true, true);
+    else if (p.xs)
+      launch_round<16, ROWS_XOR>(q, c, 0, tol, ns * ns, s, timer, true, true);
+    else
+      launch_round<16, ROWS_PER_WG>(q, c, 0, tol, ns * ns, s, timer, true, true);
+  }
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ finish
 // sigma[c] = ||W[:, c]|| for c < nc; one wave per column.
 __global__ __launch_bounds__(JNT) void jacobi_sigma_kernel(const double *__restrict__ W, int L, int nc,

@@ -187,6 +187,10 @@ struct JacobiBufs {
 // with XOR pairing a round's apply and the next round's Grams are one launch.
 hipError_t launch_jacobi_sweep(const JacobiPlan &p, const JacobiBufs &b, double tol, hipStream_t s,
                                KernelTimer *timer = nullptr);
+// Rounds between neighbouring blocks alone, passes times (0, 1), (2, 3), ...
+// and then (1, 2), (3, 4), ...
+hipError_t launch_jacobi_neighbours(const JacobiPlan &p, const JacobiBufs &b, int passes, double tol, hipStream_t s,
+                                    KernelTimer *timer = nullptr);
 // Reorder the columns of W by decreasing norm (swaps W/Wt).
 hipError_t launch_jacobi_sort_columns(const JacobiPlan &p, JacobiBufs &b, hipStream_t s);
 // Column norms, descending order, and the rank rule of Eq. (eps):
