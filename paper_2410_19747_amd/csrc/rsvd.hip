@@ -474,6 +474,12 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
   // B = Q_B R_B by CholeskyQR2 with R_B = R2 R1 kept (Q_B is not needed):
   // B's right singular vectors and values are R_B's, and the Jacobi SVD then
   // runs on the l x l R_B instead of the m x l B.
+  // Above 128 columns it runs on R_B^T as it is: Y is ordered by the power
+  // iterations, so B's columns, and more so R_B's rows, are near orthogonal,
+  // and R_B^T needs neither a QR nor the sweeps of a general matrix (256^3
+  // product at bond 128, randomized: 191 -> 156 ms).  Up to 128 columns one
+  // launch does QR and Jacobi.
+  const bool wide = l > kSvdSmallSide;
   if (!ok(launch_zero_int(b.fail2, 1, s))) return out;
   if (!ok(cholqr(b.B, m, l, spare, b.cq, b.fail2, s, timer, true))) return out;
   if (!ok(launch_copy(b.R1, b.cq.Rf, (int64_t)l * l, s))) return out;
@@ -483,7 +489,9 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
     g.M = l; g.N = l; g.K = l;
     g.A = b.cq.Rf; g.a_rs = l; g.a_cs = 1;
     g.B = b.R1; g.b_rs = l; g.b_cs = 1;
-    g.C = b.RB; g.c_rs1 = 1; g.c_cs1 = l;
+    g.C = wide ? zcur : b.RB;
+    (wide ? g.c_rs1 : g.c_cs1) = l;  // column-major R_B^T or R_B
+    (wide ? g.c_cs1 : g.c_rs1) = 1;
     Timed tm(timer, KC_GEMM, s);
     if (!ok(launch_gemm(g, s))) return out;
   }
@@ -515,8 +523,13 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
     Ysvd = b.B;
     sp = svd_plan(m, l);
   }
-  SvdResult so = svd_oside(sp, Ysvd, eps, cap, 0, max_sweeps, b.vbt, SVD_U_T, b.sig, b.svd, s, timer, trace, nullptr,
-                           b.full);
+  SvdResult so;
+  if (wide && !fail[1]) {
+    // the bases other than Y are free, at least 2 l rows each
+    so = svd_columns(zcur, spare, l, l, eps, cap, max_sweeps, b.vbt, b.sig, b.svd, s, timer, trace, b.full);
+  } else {
+    so = svd_oside(sp, Ysvd, eps, cap, 0, max_sweeps, b.vbt, SVD_U_T, b.sig, b.svd, s, timer, trace, nullptr, b.full);
+  }
   out.sweeps = so.sweeps;
   if (so.err != TTM_OK) {
     out.err = so.err;
@@ -578,8 +591,8 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
 // A capped swap of d = 8 sites keeps an eighth of its singular values, and
 // the Jacobi SVD spends its sweeps on the other seven eighths, latency bound
 // (63 rounds a sweep at 1024 columns).  Measured, products of two turbulence
-// components: 256^3 at bond 64 (512 x 512 swaps) 214 -> 86 ms, at 128
-// (1024 x 1024) 428 -> 189 ms, 128^3 at 256 (2048 x 2048) 660 -> 256 ms, and
+// components: 256^3 at bond 64 (512 x 512 swaps) 214 -> 71 ms, at 128
+// (1024 x 1024) 428 -> 121 ms, 128^3 at 256 (2048 x 2048) 660 -> 202 ms, and
 // their error against 64 bits halves (8e-14 -> 5e-14, 1.1e-13 -> 6e-14).
 // With l = 2 cap columns and M = Theta^T Theta:
 //   1. Y = orth(Theta^T Omega), then twice Y = orth(M Y); the diagonal of the
