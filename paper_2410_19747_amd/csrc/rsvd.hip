@@ -85,140 +85,354 @@ __global__ void diag_kernel(const double *__restrict__ G, int ld, int n, double 
   if (i < n) dst[i] = G[(int64_t)i * ld + i];
 }
 
-// 1 / sqrt(d) for d > 0: the hardware estimate and two Newton steps.
+// 1 / sqrt(d) for d > 0: the hardware estimate (about 2^-24 off) and one step
+// of third order.
 __device__ __forceinline__ double rsqrt_nr(double d) {
-  double y = __builtin_amdgcn_rsq(d);
-  y = y * fma(-0.5 * d * y, y, 1.5);
-  y = y * fma(-0.5 * d * y, y, 1.5);
-  return y;
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-d * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // Cholesky of the w x w diagonal block at G (row-major, ld), upper:
 // G_kk = R^T R, one workgroup, padded to CNB with the identity.  Writes
 // R^-1 (upper triangular, CNB x CNB row-major, zero below the diagonal) to
 // rinv, and R itself to rout (row-major, ld, w x w) when rout is set.  gd
+// (with nd > 0, the first block: set here, nd entries along G's diagonal)
 // holds the block's diagonal as it was before any elimination (the squared
 // column norms); a pivot at or below 64 u gd_j, or not positive, sets *fail
 // and is replaced by gd_j (or 1) so that everything stays finite.
-// Elimination of [G_kk | I] to [R | R^-T]: thread t < 256 owns the 4 x 4 tile
-// (t / 16, t % 16) of the left half in registers, thread 256 + t that of the
-// right.  Four rows per step s: the thread of tile (s, s) publishes it; the
-// threads of tile row s (two waves) factor that block U^T U and turn their
-// rows into rows of [R | R^-T] by U^-T, and publish them; the tiles below take
-// the rank-four update.  Two barriers a step.
-// Bound by the chain of the 64 pivots (a reciprocal root and its Newton steps
-// each) and 32 barriers.  Measured per block: 32 us with the inverse as
-// sixteen further steps after the factorisation; 24 us with it on threads of
-// its own but every thread factoring and solving for itself (issue bound);
-// 23 us in this form.
-__global__ __launch_bounds__(2 * CNT) void chol_diag_kernel(const double *__restrict__ G, int ld, int w,
-                                                            const double *__restrict__ gd, double *__restrict__ rinv,
-                                                            double *__restrict__ rout, int *__restrict__ fail) {
-  static_assert(CNB == 64 && CNT == 256, "one 4 x 4 tile of each half per thread");
-  __shared__ __align__(16) double rows[2][4][2 * CNB];  // four rows of [R | R^-T]
-  __shared__ __align__(16) double pblk[2][4][4];        // the pivot block
-  __shared__ double piv[CNB];
+// Elimination of [G_kk | I] to [R | X], X = R^-T, in place: G's and R's tiles
+// lie on and above the diagonal, X's on and below it, so thread t holds the
+// 4 x 4 tile (ti, tk) = (t / 16, t % 16) of G, R for tk > ti and of X for
+// tk < ti; the diagonal tile is G's up to step ti and X's from there on.
+// Four rows per step s: they are published, the tiles below take the rank-four
+// update, and the threads of row s + 1 factor the next pivot block and turn
+// their tiles into rows of R and X by its U^-T.  They do not wait for that
+// block: it was published along with row s, one update short, so its update
+// and the chain of its four pivots run among the tiles' own updates, in every
+// thread alike.  One barrier a step.
+// Bound by the chain of the 64 pivots (a reciprocal root each), sixteen
+// substitutions and barriers.  Measured per block: 32 us with the inverse as
+// sixteen further steps after the factorisation; 23 us with it on 256 threads
+// of its own and two barriers a step, and 22.5 in place with one barrier but
+// the factor after the updates; 19.7 us in this form.
+__global__ __launch_bounds__(CNT) void chol_diag_kernel(const double *__restrict__ G, int ld, int w,
+                                                        double *__restrict__ gd, int nd, double *__restrict__ rinv,
+                                                        double *__restrict__ rout, int *__restrict__ fail) {
+  static_assert(CNB == 64 && CNT == 256, "one 4 x 4 tile per thread");
+  // four rows of R and of X (zero where X has not begun), and the next pivot block
+  __shared__ __align__(16) double rrow[2][4][CNB], xrow[2][4][CNB];
+  __shared__ __align__(16) double pblk[2][4][4];
+  __shared__ __align__(16) double rdiag[CNB / 4][4][4];  // R's diagonal tiles
   typedef double d2 __attribute__((ext_vector_type(2)));
-  const bool right = threadIdx.x >= CNT;
-  const int t = threadIdx.x & (CNT - 1), ti = t >> 4, tk = t & 15, i0 = 4 * ti, k0 = 4 * tk;
-  const int kc = (right ? CNB : 0) + 2 * tk;
-  double a[4][4];
+  const int t = threadIdx.x, ti = t >> 4, tk = t & 15, i0 = 4 * ti, k0 = 4 * tk;
+  double a[4][4], lim[4], instead[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int r = 0; r < 4; ++r) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int i = i0 + r, k = k0 + c;
-      a[r][c] = (!right && i < w && k < w) ? G[(int64_t)i * ld + k] : (i == k ? 1.0 : 0.0);
+      a[r][c] = (tk >= ti && i < w && k < w) ? G[(int64_t)i * ld + k] : (i == k ? 1.0 : 0.0);
     }
-  if (threadIdx.x < CNB) piv[t] = (t < w) ? gd[t] : 1.0;
+    // a pivot at or below lim breaks down; the column's own norm takes its
+    // place, which keeps the rows behind it from growing
+    const double ref = (i0 + r < w) ? (nd ? G[(int64_t)(i0 + r) * (ld + 1)] : gd[i0 + r]) : 1.0;
+    lim[r] = 64.0 * kU * ref;
+    instead[r] = ref > 0.0 ? ref : 1.0;
+  }
+  for (int e = t; e < nd; e += CNT) gd[e] = G[(int64_t)e * (ld + 1)];
+  for (int e = t; e < 2 * 4 * CNB; e += CNT) (&xrow[0][0][0])[e] = 0.0;
   bool bad = false;
-  auto pivot = [&](double d, double ref, double &r, double &ri) {
-    const bool ok = d > 64.0 * kU * ref;  // false for NaN as well
-    bad |= !ok;
-    d = ok ? d : (ref > 0.0 ? ref : 1.0);
-    ri = rsqrt_nr(d);
-    r = d * ri;
-  };
-  // tile b of a half: its first two columns at 2b, its last two at CNB/2 + 2b,
+  // tile b of a row: its first two columns at 2b, its last two at CNB/2 + 2b,
   // so that sixteen neighbours read all banks once
-  auto put4 = [&](double (*dst)[2 * CNB], int b) {
+  auto put4 = [&](double (*dst)[CNB], int b, double (&x)[4][4]) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      *(d2 *)&dst[r][b] = d2{a[r][0], a[r][1]};
-      *(d2 *)&dst[r][b + CNB / 2] = d2{a[r][2], a[r][3]};
+      *(d2 *)&dst[r][2 * b] = d2{x[r][0], x[r][1]};
+      *(d2 *)&dst[r][2 * b + CNB / 2] = d2{x[r][2], x[r][3]};
     }
   };
-  auto get4 = [&](double (*src)[2 * CNB], int b, double (&x)[4][4]) {
+  auto get4 = [&](double (*src)[CNB], int b, double (&x)[4][4]) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const d2 lo = *(const d2 *)&src[r][b], hi = *(const d2 *)&src[r][b + CNB / 2];
+      const d2 lo = *(const d2 *)&src[r][2 * b], hi = *(const d2 *)&src[r][2 * b + CNB / 2];
       x[r][0] = lo.x; x[r][1] = lo.y; x[r][2] = hi.x; x[r][3] = hi.y;
     }
   };
-#pragma unroll 1
-  for (int st = 0; st < CNB / 4; ++st) {
-    const int j0 = 4 * st, par = st & 1;
-    if (!right && ti == st && tk == st) {
+  auto put_block = [&](double (*dst)[4]) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) pblk[par][r][c] = a[r][c];
+    for (int r = 0; r < 4; ++r) {
+      *(d2 *)&dst[r][0] = d2{a[r][0], a[r][1]};
+      *(d2 *)&dst[r][2] = d2{a[r][2], a[r][3]};
     }
-    __syncthreads();
-    if (ti == st) {
-      double p[4][4], u[4][4], iv[4];
+  };
+  auto get_block = [&](double (*src)[4], double (&x)[4][4]) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r) {
+      const d2 lo = *(const d2 *)&src[r][0], hi = *(const d2 *)&src[r][2];
+      x[r][0] = lo.x; x[r][1] = lo.y; x[r][2] = hi.x; x[r][3] = hi.y;
+    }
+  };
+  // U^T U = p (its upper triangle): U in u, the reciprocals of its diagonal
+  // in iv; whether a pivot breaks down.
+  auto factor = [&](const double (&p)[4][4], double (&u)[4][4], double (&iv)[4]) {
+    bool down = false;
 #pragma unroll
-        for (int c = r; c < 4; ++c) p[r][c] = pblk[par][r][c];
-      pivot(p[0][0], piv[j0], u[0][0], iv[0]);
+    for (int r = 0; r < 4; ++r) {
+      double d = p[r][r];
 #pragma unroll
-      for (int c = 1; c < 4; ++c) u[0][c] = p[0][c] * iv[0];
-      pivot(p[1][1] - u[0][1] * u[0][1], piv[j0 + 1], u[1][1], iv[1]);
+      for (int q = 0; q < r; ++q) d = fma(-u[q][r], u[q][r], d);
+      const bool ok = d > lim[r];  // not for a NaN
+      down |= !ok;
+      d = ok ? d : instead[r];
+      iv[r] = rsqrt_nr(d);
+      u[r][r] = d * iv[r];
 #pragma unroll
-      for (int c = 2; c < 4; ++c) u[1][c] = (p[1][c] - u[0][1] * u[0][c]) * iv[1];
-      pivot(p[2][2] - u[0][2] * u[0][2] - u[1][2] * u[1][2], piv[j0 + 2], u[2][2], iv[2]);
-      u[2][3] = (p[2][3] - u[0][2] * u[0][3] - u[1][2] * u[1][3]) * iv[2];
-      pivot(p[3][3] - u[0][3] * u[0][3] - u[1][3] * u[1][3] - u[2][3] * u[2][3], piv[j0 + 3], u[3][3], iv[3]);
-      // forward substitution of the tile's columns: x = U^-T g
+      for (int c = r + 1; c < 4; ++c) {
+        double x = p[r][c];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        a[0][c] = a[0][c] * iv[0];
-        a[1][c] = (a[1][c] - u[0][1] * a[0][c]) * iv[1];
-        a[2][c] = (a[2][c] - u[0][2] * a[0][c] - u[1][2] * a[1][c]) * iv[2];
-        a[3][c] = (a[3][c] - u[0][3] * a[0][c] - u[1][3] * a[1][c] - u[2][3] * a[2][c]) * iv[3];
+        for (int q = 0; q < r; ++q) x = fma(-u[q][r], u[q][c], x);
+        u[r][c] = x * iv[r];
       }
-      put4(rows[par], kc);
     }
-    __syncthreads();
+    return down;
+  };
+  // Row st, whose threads these are: its tiles to R and X, published.
+  auto finish_row = [&](int st, double (&u)[4][4], const double (&iv)[4]) {
+    if (tk == st) {
+      // R's tile is U itself; X's starts from the identity
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          u[r][c] = (c >= r) ? u[r][c] : 0.0;
+          a[r][c] = (c == r) ? 1.0 : 0.0;
+          rdiag[st][r][c] = u[r][c];
+        }
+      put4(rrow[st & 1], st, u);
+    }
+    // forward substitution of the tile's columns: x = U^-T g
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      a[0][c] = a[0][c] * iv[0];
+      a[1][c] = fma(-u[0][1], a[0][c], a[1][c]) * iv[1];
+      a[2][c] = fma(-u[1][2], a[1][c], fma(-u[0][2], a[0][c], a[2][c])) * iv[2];
+      a[3][c] = fma(-u[2][3], a[2][c], fma(-u[1][3], a[1][c], fma(-u[0][3], a[0][c], a[3][c]))) * iv[3];
+    }
+    put4(tk > st ? rrow[st & 1] : xrow[st & 1], tk, a);
+  };
+  if (ti == tk && ti < 2) put_block(pblk[ti ^ 1]);
+  __syncthreads();
+  if (ti == 0) {
+    double p[4][4], u[4][4], iv[4];
+    get_block(pblk[1], p);
+    bad |= factor(p, u, iv);
+    finish_row(0, u, iv);
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int st = 0; st + 1 < CNB / 4; ++st) {
+    const int par = st & 1;
     if (ti > st) {
-      double xk[4][4], xi[4][4];  // [published row][own column / own row]
-      get4(rows[par], kc, xk);
-      get4(rows[par], 2 * ti, xi);
+      double xi[4][4], xk[4][4], p[4][4], u[4][4], iv[4];  // xi, xk: [published row][own row, own column]
+      get4(rrow[par], ti, xi);
+      get_block(pblk[par], p);
+      get4(tk >= ti ? rrow[par] : xrow[par], tk, xk);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = r; c < 4; ++c)
+          p[r][c] = fma(-xi[3][r], xi[3][c], fma(-xi[2][r], xi[2][c],
+                        fma(-xi[1][r], xi[1][c], fma(-xi[0][r], xi[0][c], p[r][c]))));
+      const bool down = factor(p, u, iv);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
           a[r][c] = fma(-xi[3][r], xk[3][c], fma(-xi[2][r], xk[2][c],
                         fma(-xi[1][r], xk[1][c], fma(-xi[0][r], xk[0][c], a[r][c]))));
+      if (ti == st + 1) {
+        bad |= down;
+        finish_row(st + 1, u, iv);
+      }
+      if (ti == tk && ti == st + 2) put_block(pblk[par ^ 1]);
     }
+    __syncthreads();
   }
   if (bad) atomicOr(fail, 1);
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int c = 0; c < 4; ++c) {
+    // column k of row i of X is entry (k, i) of R^-1
+    const int k = k0 + c;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = i0 + r, k = k0 + c;
-      if (right)  // entry (i, k) of R^-T
-        rinv[k * CNB + i] = (k <= i) ? a[r][c] : 0.0;
-      else if (rout && i < w && k < w)
-        rout[(int64_t)i * ld + k] = (k >= i) ? a[r][c] : 0.0;
-    }
+    for (int r = 0; r < 4; r += 2)
+      *(d2 *)&rinv[k * CNB + i0 + r] = d2{k <= i0 + r ? a[r][c] : 0.0, k <= i0 + r + 1 ? a[r + 1][c] : 0.0};
+  }
+  if (rout) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (i0 + r < w && k0 + c < w)
+          rout[(int64_t)(i0 + r) * ld + k0 + c] = (tk > ti) ? a[r][c] : (tk == ti ? rdiag[ti][r][c] : 0.0);
+  }
 }
 
-hipError_t launch_chol_diag(const double *G, int ld, int w, const double *gd, double *rinv, double *rout,
+hipError_t launch_chol_diag(const double *G, int ld, int w, double *gd, int nd, double *rinv, double *rout,
                             int *fail, hipStream_t s) {
-  hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(2 * CNT), 0, s, G, ld, w, gd, rinv, rout, fail);
+  hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(CNT), 0, s, G, ld, w, gd, nd, rinv, rout, fail);
+  return hipGetLastError();
+}
+
+// What a diagonal block leaves to do: R_k = R_kk^-T G_k over the columns
+// behind it and G_ij -= R_ki^T R_kj over their 32 x 32 tiles on and above the
+// diagonal, one tile per workgroup.  Each workgroup forms the two 64 x 32
+// parts of R_k that its tile needs for itself (five products for the work of
+// one, on matrix cores that would idle), so that no launch stands between;
+// those of the first tile row write them to Rf.  A block's two products were
+// 4.8 us each in launches of their own; this is 7.2 us.
+constexpr int UT = 32;
+typedef double qd4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(256, 1) void chol_update_kernel(double *__restrict__ G, int l, int b0,
+                                                             const double *__restrict__ rinv,
+                                                             double *__restrict__ Rf) {
+  if (blockIdx.x < blockIdx.y) return;
+  __shared__ double R[2][CNB][UT + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lo = lane & 15, hi = lane >> 4;
+  const int c0[2] = {b0 + CNB + (int)blockIdx.y * UT, b0 + CNB + (int)blockIdx.x * UT};
+  constexpr int KQ = CNB / 4;
+  // Lane: A(lo, 4 q + hi), B(4 q + hi, lo); accumulator t: D(4 t + hi, lo).
+  double a[KQ], b[2][2][KQ];
+#pragma unroll
+  for (int q = 0; q < KQ; ++q) a[q] = rinv[(4 * q + hi) * CNB + 16 * wave + lo];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c = c0[x] + 16 * h + lo;
+#pragma unroll
+      for (int q = 0; q < KQ; ++q) b[x][h][q] = (c < l) ? G[(int64_t)(b0 + 4 * q + hi) * l + c] : 0.0;
+    }
+  // the tile's own entries: 16 x 16 of them per wave
+  const int gi = c0[0] + 16 * (wave >> 1) + hi, gj = c0[1] + 16 * (wave & 1) + lo;
+  double own[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) own[t] = (gi + 4 * t < l && gj < l) ? G[(int64_t)(gi + 4 * t) * l + gj] : 0.0;
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    qd4 d[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+      d[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[x][0][q], d[0], 0, 0, 0);
+      d[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[x][1][q], d[1], 0, 0, 0);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int m = 16 * wave + 4 * t + hi, c = c0[x] + 16 * h + lo;
+        R[x][m][16 * h + lo] = d[h][t];
+        if (x == 1 && blockIdx.y == 0 && c < l) Rf[(int64_t)(b0 + m) * l + c] = d[h][t];
+      }
+  }
+  __syncthreads();
+  qd4 d[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+  for (int q = 0; q < KQ; ++q)
+    d[q & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(R[0][4 * q + hi][16 * (wave >> 1) + lo],
+                                                    R[1][4 * q + hi][16 * (wave & 1) + lo], d[q & 1], 0, 0, 0);
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    if (gi + 4 * t < l && gj < l) G[(int64_t)(gi + 4 * t) * l + gj] = own[t] - (d[0][t] + d[1][t]);
+}
+
+// Q = Y R^-1 for 16 rows of Y per workgroup (Y, Q column-major, ld p; l
+// columns in nb blocks of CNB): the rows stay in LDS while the blocks are
+// solved, Q_k = Y_k R_kk^-1 and then Y_j -= Q_k R_kj for the blocks j > k, on
+// the matrix cores (16 x 16 tiles, one of a block's four per wave; the tiles
+// behind it dealt out to the waves).  Rf holds R's blocks above the diagonal
+// (row-major, ld l), rinv the inverses of the diagonal blocks.
+// As one product per block and per remainder the solve is 2 nb - 1 launches of
+// 4.8 us each for some hundreds of rows, bound by their latency: 34 us for
+// 1024 rows and 256 columns, here 16.6.
+constexpr int QROWS = 16;
+constexpr int kSolveCols = 1024;  // most columns whose rows fit in LDS (16 rows and a pad: 139 KB)
+template <int LC>
+__global__ __launch_bounds__(256, 1) void qsolve_kernel(const double *__restrict__ Y, int p, int l,
+                                                        const double *__restrict__ Rf,
+                                                        const double *__restrict__ rinv, double *__restrict__ Q) {
+  constexpr int P = QROWS + 1;  // LDS column stride
+  __shared__ double S[LC * P];  // column c of the rows at S[c * P]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  const int nb = (l + CNB - 1) / CNB;
+  const int r = tid & (QROWS - 1), row = blockIdx.x * QROWS + r;
+  for (int c = tid / QROWS; c < nb * CNB; c += 256 / QROWS)
+    S[c * P + r] = (row < p && c < l) ? Y[(int64_t)c * p + row] : 0.0;
+  double b[CNB / 4];  // this wave's column tile of R_kk^-1, then of R_k
+#pragma unroll
+  for (int q = 0; q < CNB / 4; ++q) b[q] = rinv[(4 * q + hi) * CNB + 16 * wave + lo];
+  __syncthreads();
+  for (int k = 0; k < nb; ++k) {
+    const int b0 = k * CNB;
+    // Lane: A(lo, 4 q + hi), B(4 q + hi, lo); accumulator t: D(4 t + hi, lo).
+    double a[CNB / 4];
+    auto load_a = [&]() {
+#pragma unroll
+      for (int q = 0; q < CNB / 4; ++q) a[q] = S[(b0 + 4 * q + hi) * P + lo];
+    };
+    auto product = [&]() {
+      qd4 x = {0.0, 0.0, 0.0, 0.0}, y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < CNB / 4; q += 2) {
+        x = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], x, 0, 0, 0);
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q + 1], b[q + 1], y, 0, 0, 0);
+      }
+      return x + y;
+    };
+    auto load_r = [&](int j0) {  // R_k over the columns of the tile at j0
+      const int j = j0 + lo;
+#pragma unroll
+      for (int q = 0; q < CNB / 4; ++q) b[q] = (j < l) ? Rf[(int64_t)(b0 + 4 * q + hi) * l + j] : 0.0;
+    };
+    load_a();
+    const qd4 qk = product();
+    int j0 = b0 + CNB + 16 * wave;  // this wave's first tile behind the block
+    if (j0 < nb * CNB) load_r(j0);
+    __syncthreads();  // the block has been read
+#pragma unroll
+    for (int t = 0; t < 4; ++t) S[(b0 + 16 * wave + lo) * P + 4 * t + hi] = qk[t];
+    __syncthreads();
+    if (j0 < nb * CNB) load_a();
+    while (j0 < nb * CNB) {
+      const qd4 d = product();
+      const int c = j0 + lo;
+      j0 += CNB;
+      if (j0 < nb * CNB) load_r(j0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) S[c * P + 4 * t + hi] -= d[t];
+    }
+    if (k + 1 < nb) {
+#pragma unroll
+      for (int q = 0; q < CNB / 4; ++q)
+        b[q] = rinv[((int64_t)(k + 1) * CNB + 4 * q + hi) * CNB + 16 * wave + lo];
+    }
+    for (int c = tid / QROWS; c < CNB; c += 256 / QROWS)
+      if (row < p && b0 + c < l) Q[(int64_t)(b0 + c) * p + row] = S[(b0 + c) * P + r];
+    __syncthreads();
+  }
+}
+hipError_t launch_qsolve(const double *Y, int p, int l, const double *Rf, const double *rinv, double *Q,
+                         hipStream_t s) {
+  const dim3 grid((p + QROWS - 1) / QROWS), block(256);
+  if (l > kSolveCols) return hipErrorInvalidValue;
+  if (l <= 128)
+    hipLaunchKernelGGL(qsolve_kernel<128>, grid, block, 0, s, Y, p, l, Rf, rinv, Q);
+  else if (l <= 256)
+    hipLaunchKernelGGL(qsolve_kernel<256>, grid, block, 0, s, Y, p, l, Rf, rinv, Q);
+  else if (l <= 512)
+    hipLaunchKernelGGL(qsolve_kernel<512>, grid, block, 0, s, Y, p, l, Rf, rinv, Q);
+  else
+    hipLaunchKernelGGL(qsolve_kernel<1024>, grid, block, 0, s, Y, p, l, Rf, rinv, Q);
   return hipGetLastError();
 }
 
@@ -274,33 +488,25 @@ hipError_t cholqr(double *Y, int p, int l, double *Q, const CqrBufs &b, int *fai
     g.part = b.part; g.part_doubles = b.part_doubles;
     if ((e = launch_gemm(g, s)) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(diag_kernel, dim3((l + 255) / 256), dim3(256), 0, s, b.G, l, l, b.gd);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   const int nb = (l + CNB - 1) / CNB;
   // Blocked Cholesky, right-looking: R_kk from the block, then
-  // R_k,rest = R_kk^-T G_k,rest and G_rest,rest -= R_k,rest^T R_k,rest.
+  // R_k,rest = R_kk^-T G_k,rest and G_rest,rest -= R_k,rest^T R_k,rest (its
+  // upper half).
   for (int kb = 0; kb < nb; ++kb) {
     const int b0 = kb * CNB, w = std::min(CNB, l - b0), rest = l - b0 - w;
     double *rk = b.rinv + (int64_t)kb * CNB * CNB;
     double *rout = want_r ? b.Rf + (int64_t)b0 * l + b0 : nullptr;
-    if ((e = launch_chol_diag(b.G + (int64_t)b0 * l + b0, l, w, b.gd + b0, rk, rout, fail, s)) != hipSuccess)
+    if ((e = launch_chol_diag(b.G + (int64_t)b0 * l + b0, l, w, b.gd + b0, kb == 0 ? l : 0, rk, rout, fail, s)) !=
+        hipSuccess)
       return e;
     if (rest == 0) break;
-    GemmArgs g;
-    g.M = w; g.N = rest; g.K = w;
-    g.A = rk; g.a_rs = 1; g.a_cs = CNB;  // (R_kk^-1)^T
-    g.B = b.G + (int64_t)b0 * l + b0 + w; g.b_rs = l; g.b_cs = 1;
-    g.C = b.Rf + (int64_t)b0 * l + b0 + w; g.c_rs1 = l; g.c_cs1 = 1;
-    if ((e = launch_gemm(g, s)) != hipSuccess) return e;
-    GemmArgs u;
-    u.M = rest; u.N = rest; u.K = w;
-    u.A = b.Rf + (int64_t)b0 * l + b0 + w; u.a_rs = 1; u.a_cs = l;
-    u.B = b.Rf + (int64_t)b0 * l + b0 + w; u.b_rs = l; u.b_cs = 1;
-    u.C = b.G + (int64_t)(b0 + w) * l + b0 + w; u.c_rs1 = l; u.c_cs1 = 1;
-    u.alpha = -1.0; u.beta = 1.0;
-    if ((e = launch_gemm(u, s)) != hipSuccess) return e;
+    const int tiles = (rest + UT - 1) / UT;
+    hipLaunchKernelGGL(chol_update_kernel, dim3(tiles, tiles), dim3(256), 0, s, b.G, l, b0, rk, b.Rf);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // Q = Y R^-1 by block columns: Q_k = Y_k R_kk^-1, then Y_rest -= Q_k R_k,rest.
+  // Q = Y R^-1 by block columns: Q_k = Y_k R_kk^-1, then Y_rest -= Q_k R_k,rest;
+  // in one launch where the rows of all blocks fit in LDS.
+  if (l <= kSolveCols) return launch_qsolve(Y, p, l, b.Rf, b.rinv, Q, s);
   for (int kb = 0; kb < nb; ++kb) {
     const int b0 = kb * CNB, w = std::min(CNB, l - b0), rest = l - b0 - w;
     GemmArgs g;
