@@ -685,7 +685,7 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
   // and R_B^T needs neither a QR nor the sweeps of a general matrix (256^3
   // product at bond 128, randomized: 191 -> 156 ms).  Up to 128 columns one
   // launch does QR and Jacobi.
-  const bool wide = l > kSvdSmallSide;
+  const bool wide = l > kColumnsSmall;
   if (!ok(launch_zero_int(b.fail2, 1, s))) return out;
   if (!ok(cholqr(b.B, m, l, spare, b.cq, b.fail2, s, timer, true))) return out;
   if (!ok(launch_copy(b.R1, b.cq.Rf, (int64_t)l * l, s))) return out;

@@ -385,10 +385,10 @@ SvdResult svd_oside(const SvdPlan &p, const double *Y, double eps, int cap, int 
   return out;
 }
 
-int svd_columns_capacity(int n, int l) { return l <= kSvdSmallSide ? l : jacobi_plan(n, l).ncp; }
+int svd_columns_capacity(int n, int l) { return l <= kColumnsSmall ? l : jacobi_plan(n, l).ncp; }
 
 size_t svd_columns_ws_doubles(int n, int l) {
-  if (l <= kSvdSmallSide)
+  if (l <= kColumnsSmall)
     return r32(std::max(qr_inplace_scratch_doubles(n, l), qr_apply_q_scratch_doubles(n, l))) +
            r32((size_t)((l + kPanel - 1) / kPanel) * kPanel * kPanel) + r32((size_t)l * l) + r32(8);
   const JacobiPlan jp = jacobi_plan(n, l);
@@ -430,7 +430,7 @@ SvdResult svd_columns(double *C, double *spare, int n, int l, double eps, int ca
     return true;
   };
   double res[8];
-  if (l <= kSvdSmallSide) {
+  if (l <= kColumnsSmall) {
     // C = Q1 R, Jacobi on R in one launch, U = Q1 U_R
     double *qr = adv(std::max(qr_inplace_scratch_doubles(n, l), qr_apply_q_scratch_doubles(n, l)));
     double *Tall = adv((size_t)((l + kPanel - 1) / kPanel) * kPanel * kPanel);
