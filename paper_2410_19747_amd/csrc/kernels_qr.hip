@@ -222,6 +222,25 @@ __device__ __forceinline__ void t_column(PanelSmem &sm, int I, int c) {
   sm.Tl[c][I] = (c < I) ? -sm.taus[I] * (a0 + a1) : (c == I ? sm.taus[I] : 0.0);
 }
 
+// As t_column for a register panel: lane c keeps row c of T in t (zero before
+// column c), I is known when compiled, so that the row of zs comes in one LDS
+// trip (with t_column's loop over LDS this was the longest part of a column).
+// The terms before column c are zeros, and the sums over even and odd b
+// commute, so the result is t_column's.
+template <int I>
+__device__ __forceinline__ void t_column_reg(const PanelSmem &sm, double (&t)[QB], int c) {
+  double a[2] = {0.0, 0.0};
+#pragma unroll
+  for (int b = 0; b < I; ++b) a[b & 1] = fma(t[b], sm.zs[I][b], a[b & 1]);
+  t[I] = (c < I) ? -sm.taus[I] * (a[0] + a[1]) : (c == I ? sm.taus[I] : 0.0);
+}
+
+// a b, rounded, whatever it is added to.
+__device__ __forceinline__ double rounded_product(double a, double b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 // Column CC of a register panel (see qr_panel_reg_kernel), one barrier.
 // The row group of 16 lanes that holds a set of rows holds all 16 columns
 // there, so lane (g, c) gets column CC at its own rows by a row broadcast
@@ -232,25 +251,37 @@ __device__ __forceinline__ void t_column(PanelSmem &sm, int I, int c) {
 // and beta, the scale is folded into the update coefficient of the columns
 // to its right and into v_c^T v_CC, and the write-out applies it once.  Row
 // sums: per lane over slots, the lane swaps over the four row groups, one
-// LDS value per (wave, column); a lane reads four of the sixteen waves'
+// LDS value per (row set, column); a lane reads four of the sixteen sets'
 // values and the lane swaps finish the sum, so every lane of a column gets
-// bitwise the same total.
-template <int SL, int CC>
-__device__ __forceinline__ void panel_column(double (&x)[SL], PanelSmem &sm, int w, int g, int c, int i0,
-                                             double &myscale, double &mybeta) {
-  constexpr int B = CC & 1;
-  // Rows at or above the pivot (< 16) occur only in slot 0.
-  double b[SL];
+// bitwise the same total, and either number of waves the same factors.
+template <int SL, int NW, int CC>
+__device__ __forceinline__ void panel_column(double (&x)[16 / NW][SL], PanelSmem &sm, double (&t)[QB], int w, int g,
+                                             int c, double &myscale, double &mybeta) {
+  constexpr int B = CC & 1, K = 16 / NW;
+  const int i0 = 4 * w + g;  // row of slot 0 of set 0
+  double b[K][SL], d[K];
 #pragma unroll
-  for (int s = 0; s < SL; ++s) b[s] = row_bcast<CC>(x[s]);
-  double dp[4] = {(i0 > CC) ? b[0] * x[0] : 0.0, 0.0, 0.0, 0.0};
+  for (int k = 0; k < K; ++k) {
 #pragma unroll
-  for (int s = 1; s < SL; ++s) dp[s & 3] = fma(b[s], x[s], dp[s & 3]);
+    for (int s = 0; s < SL; ++s) b[k][s] = row_bcast<CC>(x[k][s]);
+    // Rows at or above the pivot (< 16) occur only in slot 0 of set 0.
+    double dp[4] = {(k > 0 || i0 > CC) ? rounded_product(b[k][0], x[k][0]) : 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 1; s < SL; ++s) dp[s & 3] = fma(b[k][s], x[k][s], dp[s & 3]);
+    d[k] = (dp[0] + dp[1]) + (dp[2] + dp[3]);
+  }
   // T column CC - 2 (its zs and tau became visible at the last barrier).
-  if (CC >= 2 && w == 0 && g == 0) t_column(sm, CC - 2, c);
-  double d = rowgroup_sum((dp[0] + dp[1]) + (dp[2] + dp[3]));
-  if (g == 0) sm.red[B][w][c] = d;
-  if (i0 == CC) sm.xrow[B][c] = x[0];
+  if (CC >= 2 && w == 0) {
+    if (NW < 16) t_column_reg<(CC >= 2 ? CC - 2 : 0)>(sm, t, c);
+    else if (g == 0) t_column(sm, CC - 2, c);
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) d[k] = rowgroup_sum(d[k]);
+  if (g == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) sm.red[B][w + NW * k][c] = d[k];
+  }
+  if (i0 == CC) sm.xrow[B][c] = x[0][0];
   __syncthreads();
   const double dc = rowgroup_sum((sm.red[B][g][c] + sm.red[B][4 + g][c]) + (sm.red[B][8 + g][c] + sm.red[B][12 + g][c]));
   const double xnorm2 = row_bcast<CC>(dc);
@@ -265,9 +296,15 @@ __device__ __forceinline__ void panel_column(double (&x)[SL], PanelSmem &sm, int
   const double tot = fma(scale, dc, xc);
   // Columns right of CC: x <- x - tau (v^T x) v, v = (1 at CC, b scale below).
   const double f = (c > CC) ? tau * tot : 0.0, fs = f * scale;
-  x[0] = (i0 > CC) ? fma(-fs, b[0], x[0]) : (i0 == CC ? x[0] - f : x[0]);
 #pragma unroll
-  for (int s = 1; s < SL; ++s) x[s] = fma(-fs, b[s], x[s]);
+  for (int k = 0; k < K; ++k) {
+    if (k == 0)
+      x[0][0] = (i0 > CC) ? fma(-fs, b[0][0], x[0][0]) : (i0 == CC ? x[0][0] - f : x[0][0]);
+    else
+      x[k][0] = fma(-fs, b[k][0], x[k][0]);
+#pragma unroll
+    for (int s = 1; s < SL; ++s) x[k][s] = fma(-fs, b[k][s], x[k][s]);
+  }
   if (c == CC) {
     myscale = scale;
     mybeta = beta;
@@ -279,14 +316,23 @@ __device__ __forceinline__ void panel_column(double (&x)[SL], PanelSmem &sm, int
   }
 }
 
-template <int SL, int CC = 0>
-__device__ __forceinline__ void panel_columns(double (&x)[SL], PanelSmem &sm, int jb, int w, int g, int c, int i0,
-                                              double &myscale, double &mybeta) {
+template <int SL, int NW, int CC = 0>
+__device__ __forceinline__ void panel_columns(double (&x)[16 / NW][SL], PanelSmem &sm, double (&t)[QB], int jb, int w,
+                                              int g, int c, double &myscale, double &mybeta) {
   if constexpr (CC < QB) {
     if (CC < jb) {
-      panel_column<SL, CC>(x, sm, w, g, c, i0, myscale, mybeta);
-      panel_columns<SL, CC + 1>(x, sm, jb, w, g, c, i0, myscale, mybeta);
+      panel_column<SL, NW, CC>(x, sm, t, w, g, c, myscale, mybeta);
+      panel_columns<SL, NW, CC + 1>(x, sm, t, jb, w, g, c, myscale, mybeta);
     }
+  }
+}
+
+// Columns jb - 2 and jb - 1 of T.
+template <int I>
+__device__ __forceinline__ void t_last(const PanelSmem &sm, double (&t)[QB], int jb, int c) {
+  if constexpr (I < QB) {
+    if (I == jb - 2 || I == jb - 1) t_column_reg<I>(sm, t, c);
+    t_last<I + 1>(sm, t, jb, c);
   }
 }
 
@@ -297,12 +343,25 @@ __device__ __forceinline__ void panel_columns(double (&x)[SL], PanelSmem &sm, in
 // diagonal, v below it (the V that the updates read in place).  Also
 // writes T (16 x 16, row-major, zero outside the leading jb x jb upper
 // triangle) with H_0 H_1 ... H_{jb-1} = I - V T V^T.
-template <int SL>
-__global__ __launch_bounds__(PNT) void qr_panel_reg_kernel(double *__restrict__ S, int m, int n, int j0, int jb,
-                                                           double *__restrict__ T,
-                                                           const double *__restrict__ cnorm, int *__restrict__ perm,
-                                                           double *__restrict__ pscratch) {
-  if (cnorm) panel_pivot(S, m, n, j0, jb, cnorm, perm, pscratch);
+// Sixteen row sets, 16 / NW to a wave.  A column is bound by its chain (sum,
+// LDS, root, reciprocals) and by what every wave repeats of it; the T column
+// that wave 0 adds was a loop of LDS trips, longer than the rest.  With its
+// rows in registers and eight waves, two to a SIMD, 16 columns take 16.8 us
+// at 8 slots and 23.0 at 16, 12.0 and 13.1 at 1 and 2 (22.8, 27.1, 17.6 and
+// 18 with 16 waves and that loop; with four waves 18.9 at 8 slots and 36.5 at
+// 16, where the column's values no longer stay in registers).  Pivoted panels
+// keep the 16 waves that move their columns, whose registers leave no room
+// for T.
+template <int SL, int NW>
+__global__ __launch_bounds__(64 * NW) void qr_panel_reg_kernel(double *__restrict__ S, int m, int n, int j0, int jb,
+                                                               double *__restrict__ T,
+                                                               const double *__restrict__ cnorm,
+                                                               int *__restrict__ perm,
+                                                               double *__restrict__ pscratch) {
+  constexpr int K = 16 / NW, NTH = 64 * NW;
+  if constexpr (NTH == PNT) {
+    if (cnorm) panel_pivot(S, m, n, j0, jb, cnorm, perm, pscratch);
+  }
   __shared__ PanelSmem sm;
   // The panel passes through LDS on the way in and out, so that global
   // loads and stores run along the columns.
@@ -311,41 +370,56 @@ __global__ __launch_bounds__(PNT) void qr_panel_reg_kernel(double *__restrict__ 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
   const int mv = m - j0;
-  const int i0 = 4 * w + g;  // row of slot 0; slot s holds row i0 + 64 s
-  double x[SL];
+  const int i0 = 4 * w + g;  // row of slot 0 of set 0; slot s of set k holds row i0 + 4 NW k + 64 s
+  double x[K][SL];
 #pragma unroll
-  for (int q = 0; q < SL; ++q) {
-    const int e = tid + PNT * q, cc = e / RT, i = e % RT;
-    x[q] = (i < mv && cc < jb) ? S[(int64_t)(j0 + cc) * m + j0 + i] : 0.0;
+  for (int q = 0; q < K * SL; ++q) {
+    const int e = tid + NTH * q, cc = e / RT, i = e % RT;
+    x[q / SL][q % SL] = (i < mv && cc < jb) ? S[(int64_t)(j0 + cc) * m + j0 + i] : 0.0;
   }
 #pragma unroll
-  for (int q = 0; q < SL; ++q) {
-    const int e = tid + PNT * q;
-    tile[e / RT][e % RT] = x[q];
+  for (int q = 0; q < K * SL; ++q) {
+    const int e = tid + NTH * q;
+    tile[e / RT][e % RT] = x[q / SL][q % SL];
   }
-  if (w == 0 && g == 0)
+  if (NW == 16 && w == 0 && g == 0)
     for (int b = 0; b < QB; ++b) sm.Tl[c][b] = 0.0;
   __syncthreads();
 #pragma unroll
-  for (int s = 0; s < SL; ++s) x[s] = tile[c][i0 + 64 * s];
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int s = 0; s < SL; ++s) x[k][s] = tile[c][i0 + 4 * NW * k + 64 * s];
   double myscale = 0.0, mybeta = 0.0;  // of this lane's column once reflected
-  panel_columns<SL>(x, sm, jb, w, g, c, i0, myscale, mybeta);
+  double t[QB];  // row c of T (wave 0)
+#pragma unroll
+  for (int b = 0; b < QB; ++b) t[b] = 0.0;
+  panel_columns<SL, NW>(x, sm, t, jb, w, g, c, myscale, mybeta);
   // Column c: R above row c, beta at row c, v = x scale below.
 #pragma unroll
-  for (int s = 0; s < SL; ++s) {
-    const int i = i0 + 64 * s;
-    tile[c][i] = (i > c) ? x[s] * myscale : (i == c ? mybeta : x[s]);
-  }
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      const int i = i0 + 4 * NW * k + 64 * s;
+      tile[c][i] = (i > c) ? x[k][s] * myscale : (i == c ? mybeta : x[k][s]);
+    }
   __syncthreads();
   // The last two columns of T, then T out.
-  if (w == 0 && g == 0) {
-    if (jb >= 2) t_column(sm, jb - 2, c);
-    t_column(sm, jb - 1, c);
-    for (int b = 0; b < QB; ++b) T[c * QB + b] = (c < jb && b < jb) ? sm.Tl[c][b] : 0.0;
+  if (w == 0) {
+    if (NW < 16) {
+      t_last<0>(sm, t, jb, c);
+      if (g == 0) {
+#pragma unroll
+        for (int b = 0; b < QB; ++b) T[c * QB + b] = (c < jb && b < jb) ? t[b] : 0.0;
+      }
+    } else if (g == 0) {
+      if (jb >= 2) t_column(sm, jb - 2, c);
+      t_column(sm, jb - 1, c);
+      for (int b = 0; b < QB; ++b) T[c * QB + b] = (c < jb && b < jb) ? sm.Tl[c][b] : 0.0;
+    }
   }
 #pragma unroll
-  for (int q = 0; q < SL; ++q) {
-    const int e = tid + PNT * q, cc = e / RT, i = e % RT;
+  for (int q = 0; q < K * SL; ++q) {
+    const int e = tid + NTH * q, cc = e / RT, i = e % RT;
     if (i < mv) {
       const double val = tile[cc][i];
       if (cc < jb) S[(int64_t)(j0 + cc) * m + j0 + i] = val;
@@ -1170,11 +1244,16 @@ hipError_t launch_panel(double *S, int m, int n, int j0, int jb, double *T, cons
   const int sl = (m - j0 + 63) / 64;
   const dim3 g(1), b(PNT);
 #define TTM_PANEL_ARGS S, m, n, j0, jb, T, pv.cnorm, pv.perm, pv.scratch
-  if (sl <= 1) hipLaunchKernelGGL(qr_panel_reg_kernel<1>, g, b, 0, s, TTM_PANEL_ARGS);
-  else if (sl <= 2) hipLaunchKernelGGL(qr_panel_reg_kernel<2>, g, b, 0, s, TTM_PANEL_ARGS);
-  else if (sl <= 4) hipLaunchKernelGGL(qr_panel_reg_kernel<4>, g, b, 0, s, TTM_PANEL_ARGS);
-  else if (sl <= 8) hipLaunchKernelGGL(qr_panel_reg_kernel<8>, g, b, 0, s, TTM_PANEL_ARGS);
-  else if (sl <= MAX_REG_SLOTS) hipLaunchKernelGGL(qr_panel_reg_kernel<16>, g, b, 0, s, TTM_PANEL_ARGS);
+#define TTM_PANEL_REG(SL, NW) \
+  do { \
+    if (pv.cnorm) hipLaunchKernelGGL((qr_panel_reg_kernel<SL, 16>), g, b, 0, s, TTM_PANEL_ARGS); \
+    else hipLaunchKernelGGL((qr_panel_reg_kernel<SL, NW>), g, dim3(64 * NW), 0, s, TTM_PANEL_ARGS); \
+  } while (0)
+  if (sl <= 1) TTM_PANEL_REG(1, 8);
+  else if (sl <= 2) TTM_PANEL_REG(2, 8);
+  else if (sl <= 4) TTM_PANEL_REG(4, 8);
+  else if (sl <= 8) TTM_PANEL_REG(8, 8);
+  else if (sl <= MAX_REG_SLOTS) TTM_PANEL_REG(16, 8);
   else if (sl <= 2 * MAX_REG_SLOTS) hipLaunchKernelGGL(qr_panel_ext_kernel, g, b, 0, s, TTM_PANEL_ARGS);
   else {
     if (coop && !pv.cnorm) {
@@ -1186,6 +1265,7 @@ hipError_t launch_panel(double *S, int m, int n, int j0, int jb, double *T, cons
     }
     hipLaunchKernelGGL(qr_panel_mem_kernel, g, b, 0, s, TTM_PANEL_ARGS);
   }
+#undef TTM_PANEL_REG
 #undef TTM_PANEL_ARGS
   return hipGetLastError();
 }
