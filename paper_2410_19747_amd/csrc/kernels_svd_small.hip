@@ -13,7 +13,10 @@
 // Layout (LN lanes per row group, NW waves): lane l holds columns 4u .. 4u + 3,
 // u = l mod LN, as two units of two columns (A: 0, 1; B: 2, 3); the H = 64 / LN
 // lane groups and the waves split the rows: group q = w H + l / LN holds the
-// rows i Q + q, i < RL, with Q = NW H.  The tile is N = 4 LN columns by N rows.
+// rows i Q + q, i < RL, with Q = NW H.  The tile is N = 4 LN columns by as many
+// rows, or by 96 for sides of 65 to 96, which need no more (a step's dot
+// products and rotations then run over three quarters of the rows: 1223 ->
+// 988 us at 96 columns).
 //
 // What bounds it is the issue and the latency of one wave per SIMD (an
 // instruction issues in 4 cycles, an FP64 result returns after about 10, a
@@ -30,7 +33,7 @@
 //    against 780, 1150 and 1910.
 // Measured, a k x k matrix with values i^-2, whole SVD with its read-back, by
 // the block method and here: k = 8: 446 and 71 us, 16: 522 and 79, 32: 646 and
-// 146, 64: 988 and 367, 96: 1476 and 1223, 128: 2168 and 1261; 64 x 512: 1065
+// 146, 64: 988 and 367, 96: 1476 and 988, 128: 2168 and 1261; 64 x 512: 1065
 // and 524, 1024 x 128: 2162 and 1368.  Of it the QR takes 680, 1490, 2150 and
 // 3500 cycles a column and a sweep 10.9, 27, 77 and 261 thousand at 16, 32, 64
 // and 128 columns (with each sum of a QR step read from LDS behind the store
@@ -46,19 +49,20 @@ namespace ttm {
 namespace {
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-template <int LN, int NW>
+template <int LN, int NW, int ROWS>
 struct SmallTile {
   static constexpr int H = 64 / LN;   // lanes of a wave that share a unit pair
-  static constexpr int N = 4 * LN;    // columns and rows of the tile
+  static constexpr int N = 4 * LN;    // columns of the tile
   static constexpr int Q = NW * H;    // row groups
-  static constexpr int RL = N / Q;    // rows of a lane
-  static constexpr int LD = N + 1;    // LDS column stride (odd: lanes of different columns hit different banks)
+  static constexpr int RL = ROWS / Q;  // rows of a lane
+  static constexpr int CL = N / Q;     // columns that a row group counts for the order
+  static constexpr int LD = ROWS + 1;    // LDS column stride (odd: lanes of different columns hit different banks)
   static constexpr int NT = 64 * NW;  // threads
 };
 
-template <int LN, int NW>
+template <int LN, int NW, int ROWS>
 struct SmallSmem {
-  typedef SmallTile<LN, NW> T;
+  typedef SmallTile<LN, NW, ROWS> T;
   double W[T::N * T::LD];       // columns of the matrix, staged
   __align__(16) double part[2][NW][T::N];  // per-wave sums of the columns (or of the pairs), double-buffered
   __align__(16) double row[2][T::N];       // the pivot row of a QR step
@@ -138,14 +142,14 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // One workgroup's state: the tile and this lane's place in it.
-template <int LN, int NW>
+template <int LN, int NW, int ROWS>
 struct Small {
-  typedef SmallTile<LN, NW> T;
-  SmallSmem<LN, NW> &sm;
+  typedef SmallTile<LN, NW, ROWS> T;
+  SmallSmem<LN, NW, ROWS> &sm;
   int lane, w, u, h, q;
   double x[4][T::RL];
 
-  __device__ __forceinline__ explicit Small(SmallSmem<LN, NW> &s) : sm(s) {
+  __device__ __forceinline__ explicit Small(SmallSmem<LN, NW, ROWS> &s) : sm(s) {
     lane = threadIdx.x & 63;
     w = threadIdx.x >> 6;
     u = lane % LN;
@@ -213,16 +217,16 @@ struct Small {
   // them; a column's place is the sum over the groups (at most 127, four
   // columns to a word).
   __device__ __forceinline__ void order() {
-    double me[4], o[T::RL];
+    double me[4], o[T::CL];
     get4(&sm.norm[4 * u], me);
 #pragma unroll
-    for (int i = 0; i < T::RL; ++i) o[i] = sm.norm[i * T::Q + q];
+    for (int i = 0; i < T::CL; ++i) o[i] = sm.norm[i * T::Q + q];
     unsigned pos = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       unsigned cnt = 0;
 #pragma unroll
-      for (int i = 0; i < T::RL; ++i)
+      for (int i = 0; i < T::CL; ++i)
         cnt += (unsigned)((o[i] > me[e]) | ((o[i] == me[e]) & (i * T::Q + q < 4 * u + e)));
       pos |= cnt << (8 * e);
     }
@@ -378,7 +382,7 @@ struct Small {
           for (int e = 0; e < 4; ++e) x[e][i] = fma(-f[e], vv[i], x[e][i]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e][I] = mine ? 0.0 : x[e][I];
-        if (mine) {
+        if (mine && 4 * u < ROWS) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) sm.W[j * T::LD + 4 * u + e] = rc[e];
         }
@@ -394,7 +398,7 @@ struct Small {
     qr_rows<0>(kk, left);
     __syncthreads();
 #pragma unroll 1
-    for (int e = threadIdx.x; e < (T::N - kk) * T::N; e += T::NT) sm.W[(kk + e / T::N) * T::LD + e % T::N] = 0.0;
+    for (int e = threadIdx.x; e < (T::N - kk) * ROWS; e += T::NT) sm.W[(kk + e / ROWS) * T::LD + e % ROWS] = 0.0;
   }
 
   // Limits of a sweep: the noise level thr of a squared norm, tol^2, the
@@ -525,28 +529,28 @@ struct Small {
   }
 };
 
-template <int LN, int NW, int MODE>
+template <int LN, int NW, int ROWS, int MODE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1))) void svd_small_kernel(SvdSmall a) {
-  typedef SmallTile<LN, NW> T;
-  __shared__ SmallSmem<LN, NW> sm;
-  Small<LN, NW> s(sm);
+  typedef SmallTile<LN, NW, ROWS> T;
+  __shared__ SmallSmem<LN, NW, ROWS> sm;
+  Small<LN, NW, ROWS> s(sm);
   const int tid = threadIdx.x;
   // tolerance and noise level of a k-row Jacobi (see kernels_svd.hip)
   const double tol = sqrt((double)a.k) * 2.220446049250313e-16, noise = 8.0 * tol;
   // 1. stage the source, column by column
   if (MODE == SMALL_Y) {
-    for (int e = tid; e < T::N * T::N; e += T::NT) {
-      const int c = e / T::N, r = e % T::N;
+    for (int e = tid; e < T::N * ROWS; e += T::NT) {
+      const int c = e / ROWS, r = e % ROWS;
       sm.W[c * T::LD + r] = (r < a.np && c < a.no) ? a.src[(int64_t)c * a.ld + r] : 0.0;
     }
   } else if (MODE == SMALL_R) {
-    for (int e = tid; e < T::N * T::N; e += T::NT) {
-      const int j = e / T::N, c = e % T::N;
+    for (int e = tid; e < T::N * ROWS; e += T::NT) {
+      const int j = e / ROWS, c = e % ROWS;
       sm.W[j * T::LD + c] = (j < a.k && c <= j) ? a.src[(int64_t)j * a.ld + c] : 0.0;
     }
   } else {
     // column c of W (or of the matrix that QR takes) is row c of R
-    for (int e = tid; e < T::N * T::N; e += T::NT) {
+    for (int e = tid; e < T::N * ROWS; e += T::NT) {
       const int j = e / T::N, c = e % T::N;  // entry (c, j) of R, c <= j, along a column of S
       sm.W[c * T::LD + j] = (j < a.k && c <= j) ? a.src[(int64_t)j * a.ld + c] : 0.0;
     }
@@ -695,16 +699,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
 }
 
-template <int LN, int NW>
+template <int LN, int NW, int ROWS>
 void launch_mode(const SvdSmall &a, hipStream_t s) {
   if (a.mode == SMALL_Y)
-    hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_Y>), dim3(1), dim3(64 * NW), 0, s, a);
+    hipLaunchKernelGGL((svd_small_kernel<LN, NW, ROWS, SMALL_Y>), dim3(1), dim3(64 * NW), 0, s, a);
   else if (a.mode == SMALL_RT)
-    hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_RT>), dim3(1), dim3(64 * NW), 0, s, a);
+    hipLaunchKernelGGL((svd_small_kernel<LN, NW, ROWS, SMALL_RT>), dim3(1), dim3(64 * NW), 0, s, a);
   else if (a.mode == SMALL_RTQ)
-    hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_RTQ>), dim3(1), dim3(64 * NW), 0, s, a);
+    hipLaunchKernelGGL((svd_small_kernel<LN, NW, ROWS, SMALL_RTQ>), dim3(1), dim3(64 * NW), 0, s, a);
   else
-    hipLaunchKernelGGL((svd_small_kernel<LN, NW, SMALL_R>), dim3(1), dim3(64 * NW), 0, s, a);
+    hipLaunchKernelGGL((svd_small_kernel<LN, NW, ROWS, SMALL_R>), dim3(1), dim3(64 * NW), 0, s, a);
 }
 }  // namespace
 
@@ -712,13 +716,15 @@ hipError_t launch_svd_small(const SvdSmall &a, hipStream_t s) {
   const int side = (a.mode == SMALL_Y) ? (a.np > a.no ? a.np : a.no) : a.k;
   if (a.k < 1 || side > kSvdSmallSide || a.mode < SMALL_Y || a.mode > SMALL_R) return hipErrorInvalidValue;
   if (side <= 16)
-    launch_mode<4, 1>(a, s);
+    launch_mode<4, 1, 16>(a, s);
   else if (side <= 32)
-    launch_mode<8, 1>(a, s);
+    launch_mode<8, 1, 32>(a, s);
   else if (side <= 64)
-    launch_mode<16, 4>(a, s);
+    launch_mode<16, 4, 64>(a, s);
+  else if (side <= 96)
+    launch_mode<32, 4, 96>(a, s);
   else
-    launch_mode<32, 4>(a, s);
+    launch_mode<32, 4, 128>(a, s);
   return hipGetLastError();
 }
 

@@ -1318,6 +1318,10 @@ int run_conventional_impl(const ttm_tt *A, const ttm_tt *B, int chi_out, double 
     g.A = T2; g.a_rs = ar * br; g.a_cs = 1;
     g.B = Rv[i + 1]; g.b_rs = 1; g.b_cs = ar * br;
     g.C = out; g.c_rs1 = cr; g.c_cs1 = 1;
+    // few outputs, a long sum (512 x 64 over 4096 at bond 64): T1 has been
+    // read and holds the partial sums of a split over K (43 us unsplit,
+    // 12.6 and 6 us split)
+    g.part = T1; g.part_doubles = pl.tmax;
     R.gemm(g);
   };
 

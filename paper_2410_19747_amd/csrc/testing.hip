@@ -12,8 +12,10 @@ typedef double dbl4_t __attribute__((ext_vector_type(4)));
 // FP64 matrix-core rate probe: every wave runs eight independent chains of
 // v_mfma_f64_16x16x4f64 (2048 flops each) on register operands, so the
 // issue rate of the matrix cores is the only limit; the accumulators are
-// written out so that nothing is optimised away.
-__global__ __launch_bounds__(256) void mfma_f64_rate_kernel(int iters, double *__restrict__ out) {
+// written out so that nothing is optimised away.  Two waves to a SIMD at
+// least, or the compiler puts the accumulators in AGPRs, where an instruction
+// takes 138 cycles for 64 (50 TFLOP/s for 73).
+__global__ __launch_bounds__(256, 2) void mfma_f64_rate_kernel(int iters, double *__restrict__ out) {
   const double a = 1.0 + 1e-3 * (threadIdx.x & 63), b = 1.0 - 1e-3 * (threadIdx.x & 63);
   constexpr int CH = 8;
   dbl4_t acc[CH];

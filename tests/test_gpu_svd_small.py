@@ -60,7 +60,7 @@ def _matrix(kind, m, n, rng):
 
 SIZES = [(1, 1), (2, 1), (1, 7), (3, 3), (16, 16), (31, 32), (32, 32), (33, 17), (40, 33), (64, 64), (63, 65), (65, 64),
          (96, 97), (127, 128), (128, 128), (1, 300), (300, 1), (129, 16), (20, 130), (500, 33), (64, 512), (1000, 65),
-         (128, 1024), (513, 128), (127, 129)]
+         (128, 1024), (513, 128), (127, 129), (95, 96), (96, 70), (97, 97), (96, 400), (400, 96), (97, 300)]
 
 
 @pytest.mark.parametrize("right_pow", [0, 1])
