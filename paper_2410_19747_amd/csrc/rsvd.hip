@@ -863,7 +863,8 @@ bool psvd_eligible(int m, int n, int cap) {
   // the discarded weight is summed over at most six blocks of columns
   const int room = psvd_columns(m, n, l);
   if ((n + room - 1) / room > 6) return false;
-  return psvd_part_doubles(m, n, cap) >= 4 * (int64_t)l * l;
+  // scratch for a Gram split in four, or all that a split ever takes
+  return psvd_part_doubles(m, n, cap) >= std::min<int64_t>(kGramPart, 4 * (int64_t)l * l);
 }
 
 PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
