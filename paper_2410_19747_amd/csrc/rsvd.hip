@@ -100,7 +100,8 @@ __device__ __forceinline__ double rsqrt_nr(double d) {
 // (with nd > 0, the first block: set here, nd entries along G's diagonal)
 // holds the block's diagonal as it was before any elimination (the squared
 // column norms); a pivot at or below 64 u gd_j, or not positive, sets *fail
-// and is replaced by gd_j (or 1) so that everything stays finite.
+// and is replaced by gd_j (or 1) so that everything stays finite.  shift gd_j
+// is added to the diagonal first.
 // Elimination of [G_kk | I] to [R | X], X = R^-T, in place: G's and R's tiles
 // lie on and above the diagonal, X's on and below it, so thread t holds the
 // 4 x 4 tile (ti, tk) = (t / 16, t % 16) of G, R for tk > ti and of X for
@@ -117,7 +118,8 @@ __device__ __forceinline__ double rsqrt_nr(double d) {
 // of its own and two barriers a step, and 22.5 in place with one barrier but
 // the factor after the updates; 19.7 us in this form.
 __global__ __launch_bounds__(CNT) void chol_diag_kernel(const double *__restrict__ G, int ld, int w,
-                                                        double *__restrict__ gd, int nd, double *__restrict__ rinv,
+                                                        double *__restrict__ gd, int nd, double shift,
+                                                        double *__restrict__ rinv,
                                                         double *__restrict__ rout, int *__restrict__ fail) {
   static_assert(CNB == 64 && CNT == 256, "one 4 x 4 tile per thread");
   // four rows of R and of X (zero where X has not begun), and the next pivot block
@@ -137,6 +139,7 @@ __global__ __launch_bounds__(CNT) void chol_diag_kernel(const double *__restrict
     // a pivot at or below lim breaks down; the column's own norm takes its
     // place, which keeps the rows behind it from growing
     const double ref = (i0 + r < w) ? (nd ? G[(int64_t)(i0 + r) * (ld + 1)] : gd[i0 + r]) : 1.0;
+    if (ti == tk) a[r][r] = fma(shift, ref, a[r][r]);
     lim[r] = 64.0 * kU * ref;
     instead[r] = ref > 0.0 ? ref : 1.0;
   }
@@ -278,9 +281,9 @@ __global__ __launch_bounds__(CNT) void chol_diag_kernel(const double *__restrict
   }
 }
 
-hipError_t launch_chol_diag(const double *G, int ld, int w, double *gd, int nd, double *rinv, double *rout,
-                            int *fail, hipStream_t s) {
-  hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(CNT), 0, s, G, ld, w, gd, nd, rinv, rout, fail);
+hipError_t launch_chol_diag(const double *G, int ld, int w, double *gd, int nd, double shift, double *rinv,
+                            double *rout, int *fail, hipStream_t s) {
+  hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(CNT), 0, s, G, ld, w, gd, nd, shift, rinv, rout, fail);
   return hipGetLastError();
 }
 
@@ -473,8 +476,11 @@ CqrBufs cqr_carve(int l, double *base, int64_t part = kGramPart) {
 // p x l (ld p).  Y is overwritten (the block solve updates it in place).
 // With want_r, b.Rf holds all of R afterwards (row-major, zero below the
 // diagonal); otherwise only its blocks right of the diagonal blocks.
+// With a shift, shift times each column's squared norm is added to the Gram's
+// diagonal: no pivot breaks down, and Q is orthonormal only as far as the
+// shift allows (further passes make it so).
 hipError_t cholqr(double *Y, int p, int l, double *Q, const CqrBufs &b, int *fail, hipStream_t s,
-                  KernelTimer *timer, bool want_r = false) {
+                  KernelTimer *timer, bool want_r = false, double shift = 0.0) {
   Timed tm(timer, KC_QR, s);
   hipError_t e;
   if (want_r && (e = launch_fill(b.Rf, 0.0, (int64_t)l * l, s)) != hipSuccess) return e;
@@ -496,8 +502,8 @@ hipError_t cholqr(double *Y, int p, int l, double *Q, const CqrBufs &b, int *fai
     const int b0 = kb * CNB, w = std::min(CNB, l - b0), rest = l - b0 - w;
     double *rk = b.rinv + (int64_t)kb * CNB * CNB;
     double *rout = want_r ? b.Rf + (int64_t)b0 * l + b0 : nullptr;
-    if ((e = launch_chol_diag(b.G + (int64_t)b0 * l + b0, l, w, b.gd + b0, kb == 0 ? l : 0, rk, rout, fail, s)) !=
-        hipSuccess)
+    if ((e = launch_chol_diag(b.G + (int64_t)b0 * l + b0, l, w, b.gd + b0, kb == 0 ? l : 0, shift, rk, rout, fail,
+                              s)) != hipSuccess)
       return e;
     if (rest == 0) break;
     const int tiles = (rest + UT - 1) / UT;
@@ -825,6 +831,16 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
 namespace {
 constexpr int PSVD_POWER = 2;     // plain iterations before the filter
 constexpr int MAX_FILTER = 10;    // beyond it the full SVD costs no more
+// A spectrum that falls by more than about 1e7 over the sketch breaks a
+// CholeskyQR down.  The swap then starts again with half steps Y -> Theta Y ->
+// Theta^T Theta Y, each orthonormalised by two passes with this shift of the
+// Gram's diagonal and a plain one (shifted CholeskyQR3, Fukaya, Kannan,
+// Nakatsukasa, Yamamoto and Yanagisawa 2020; the shift, well above the Gram's
+// own rounding, bounds what a pass leaves).  Two swaps in 22 of a 256^3
+// product at bond 128 come to that (512 x 1024: 121 -> 113 ms a product, the
+// full SVD having taken them before), seven in 30 of a 1024^3 product at bond
+// 512 (4096 x 4096: 3646 -> 1838 ms).
+constexpr double STEEP_SHIFT = 1e-12;
 
 struct PsvdBufs {
   double *Y, *W, *Z, *T, *vt, *small, *full, *diag;
@@ -867,8 +883,9 @@ bool psvd_eligible(int m, int n, int cap) {
   return psvd_part_doubles(m, n, cap) >= std::min<int64_t>(kGramPart, 4 * (int64_t)l * l);
 }
 
-PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
-                      double *ws, hipStream_t s, KernelTimer *timer, int trace) {
+namespace {
+PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
+                    double *ws, hipStream_t s, KernelTimer *timer, int trace, bool steep) {
   PsvdResult out;
   const int l = rsvd_sketch_cols(cap);
   const int64_t part = psvd_part_doubles(m, n, cap);
@@ -911,13 +928,22 @@ PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, in
   };
   auto refuse = [&](const char *why, double v) {
     out.fallback = true;
-    if (trace) fprintf(stderr, "[ttm] psvd %dx%d cap %d: %s (%.2e), full SVD instead\n", m, n, cap, why, v);
+    if (trace)
+      fprintf(stderr, "[ttm] psvd %dx%d cap %d: %s (%.2e), %s instead\n", m, n, cap, why, v,
+              out.breakdown && !steep ? "shifted passes" : "full SVD");
     return out;
   };
   double *ycur = b.Y, *wcur = b.W, *zcur = b.Z, *spare = b.T;
   auto orth = [&](double *&X, int p, bool diag = false) {
-    if (!ok(cholqr(X, p, l, spare, b.cq, b.fail, s, timer, diag))) return false;
-    std::swap(X, spare);
+    for (int pass = steep ? 0 : 2; pass < 3; ++pass) {
+      const bool first = pass == (steep ? 0 : 2);
+      if (!ok(cholqr(X, p, l, spare, b.cq, b.fail, s, timer, diag && first, pass < 2 ? STEEP_SHIFT : 0.0))) return false;
+      std::swap(X, spare);
+      if (diag && first) {
+        hipLaunchKernelGGL(diag_kernel, dim3((l + 255) / 256), dim3(256), 0, s, b.cq.Rf, l, l, b.diag);
+        if (!ok(hipGetLastError())) return false;
+      }
+    }
     return true;
   };
   // out = alpha Theta in (m x l) or alpha Theta^T in (n x l), plus beta out
@@ -957,20 +983,25 @@ PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, in
   if (!prod(true, zcur, ycur) || !orth(ycur, n)) return out;
   for (int it = 0; it < PSVD_POWER; ++it) {
     const bool last = it + 1 == PSVD_POWER;
-    if (!prod(false, ycur, zcur) || !prod(true, zcur, ycur) || !orth(ycur, n, last)) return out;
+    if (!prod(false, ycur, zcur) || (steep && !orth(zcur, m))) return out;
+    if (!prod(true, zcur, ycur) || !orth(ycur, n, last)) return out;
   }
   std::vector<double> h(l);
   double tot = 0.0;
   int fail = 0;
-  hipLaunchKernelGGL(diag_kernel, dim3((l + 255) / 256), dim3(256), 0, s, b.cq.Rf, l, l, b.diag);
-  if (!ok(hipGetLastError())) return out;
   if (!ok(hipMemcpyAsync(h.data(), b.diag, sizeof(double) * l, hipMemcpyDeviceToHost, s))) return out;
   if (!ok(hipMemcpyAsync(&tot, b.full, sizeof(double), hipMemcpyDeviceToHost, s))) return out;
   if (!ok(hipMemcpyAsync(&fail, b.fail, sizeof(int), hipMemcpyDeviceToHost, s))) return out;
   if (!sync()) return out;
+  out.breakdown = fail != 0;
   if (fail) return refuse("CholeskyQR breakdown", fail);
+  if (steep)  // of Theta^T Z, not of M Y
+    for (double &x : h) x *= x;
   std::sort(h.begin(), h.end(), [](double x, double y) { return x > y; });
   const double bnd = h[l - 1], kept = h[cap - 1];
+  // the shift hides where the spectrum ends: that the full SVD decides
+  const double noise = 100.0 * 8.0 * sqrt((double)std::min(m, n)) * kU;
+  if (steep && !(kept > noise * noise * tot)) return refuse("the cap lies in the noise", kept / tot);
   // 2. the filter: each raises the cap-th direction over the rest by
   // 2 x^2 - 1; the start has raised it by (kept / bnd)^(power + 1/2).  What
   // is asked for is 1e-18 of ||Theta||_F: the estimates are a little rough, and
@@ -993,11 +1024,12 @@ PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, in
   if (!ok(hipMemcpyAsync(&fail, b.fail, sizeof(int), hipMemcpyDeviceToHost, s))) return out;
   SvdResult so = svd_columns(ycur, wcur, n, l, eps, cap, max_sweeps, pt, b.diag, b.svd, s, timer, trace, b.full);
   out.sweeps = so.sweeps;
+  out.breakdown = fail != 0;
+  if (fail && so.err != TTM_EHIP) return refuse("CholeskyQR breakdown", fail);
   if (so.err != TTM_OK) {
     out.err = so.err;
     return out;
   }
-  if (fail) return refuse("CholeskyQR breakdown", fail);
   const int r = so.rank;
   // X' = Theta V_r (m x r, row-major); what the triplets miss; the weight discarded
   {
@@ -1061,6 +1093,15 @@ PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, in
   if (trace)
     fprintf(stderr, "[ttm] psvd %dx%d l=%d filters=%d sweeps=%d rank=%d missed=%.2e disc=%.3e total=%.3e\n", m, n, l,
             filters, out.sweeps, r, out.missed, disc, tot);
+  return out;
+}
+}  // namespace
+
+PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
+                      double *ws, hipStream_t s, KernelTimer *timer, int trace) {
+  PsvdResult out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, false);
+  if (out.breakdown && out.err == TTM_OK)
+    out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, true);
   return out;
 }
 

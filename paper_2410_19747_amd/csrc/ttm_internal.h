@@ -359,6 +359,7 @@ struct PsvdResult {
   double missed = 0.0;  // ||(I - Z Z^T) Theta V_r||_F / ||Theta||_F
   int sweeps = 0, filters = 0;
   bool fallback = false;
+  bool breakdown = false;  // a CholeskyQR met a numerically dependent column
   int err = 0;
 };
 bool psvd_eligible(int m, int n, int cap);

@@ -131,3 +131,19 @@ def test_refused_or_right(kind):
         sv = np.linalg.svd(M, compute_uv=False)
         assert r == cap
         assert abs(np.linalg.norm(M - xt @ pt) - np.linalg.norm(sv[r:])) <= 200 * U * np.linalg.norm(sv)
+
+
+@pytest.mark.parametrize("m,n,cap,rate", [(256, 256, 40, 0.2), (200, 260, 33, 0.25), (300, 256, 64, 0.12),
+                                          (512, 1024, 128, 0.06)])
+def test_spectrum_steeper_than_the_grams_resolve(m, n, cap, rate):
+    """Values 10^(-rate i): those at the end of the 2 cap sketch columns are
+    below u of the first, so that a plain CholeskyQR breaks down; the kept ones
+    are above the noise level, and the passes with a shift must find them."""
+    s = 10.0 ** (-rate * np.arange(min(m, n)))
+    M, _, _ = _with_values(m, n, s, 11)
+    got = _capped(M, cap, 1e-30)
+    assert got is not None
+    pt, xt, r, w = got
+    assert r == cap and np.abs(pt @ pt.T - np.eye(r)).max() <= 64 * 2 * cap * U
+    best = np.sqrt((s[cap:] ** 2).sum())
+    assert abs(np.linalg.norm(M - xt @ pt) - best) <= 200 * U * np.linalg.norm(s)
