@@ -11,8 +11,8 @@
 //   2. q times: Z = orth(Theta Y), Y = orth(Theta^T Z); then a second
 //      orthonormalisation pass on Y;
 //   3. B = Theta Y (m x l, FP64) = Q_B R_B by CholeskyQR2, and the SVD of
-//      the l x l factor R_B (B's values and right vectors V_B) by the
-//      one-sided Jacobi driver (svd_oside);
+//      the l x l factor R_B (B's values and right vectors V_B) by
+//      one-sided Jacobi, above 64 columns on R_B^T as it is (svd_columns);
 //   4. the rule of Eq. (eps) on those values with the weight that the l
 //      directions do not capture, ||Theta||_F^2 - ||B||_F^2, added to every
 //      tail;
@@ -24,8 +24,8 @@
 // subspace.  orth() is one CholeskyQR pass (G = Y^T Y = R^T R, Y <- Y R^-1)
 // on the intermediate bases and two (CholeskyQR2; Yamamoto et al., ETNA 44
 // (2015)) on the final one, all in FP64: a blocked Cholesky (one workgroup
-// per 64 x 64 diagonal block, matrix-core products for the panels and
-// trailing updates) and a blocked triangular solve.  CholeskyQR needs
+// per 64 x 64 diagonal block, one launch for what the block leaves) and a
+// triangular solve in one launch.  CholeskyQR needs
 // kappa(Y) well below u^(-1/2); a pivot that falls to the rounding level of
 // its column's norm (rank-deficient Theta, or kappa(Y) beyond ~1e7) raises
 // a flag, and the caller then runs the full SVD on the same matrix instead.
@@ -803,8 +803,9 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
 // A capped swap of d = 8 sites keeps an eighth of its singular values, and
 // the Jacobi SVD spends its sweeps on the other seven eighths, latency bound
 // (63 rounds a sweep at 1024 columns).  Measured, products of two turbulence
-// components: 256^3 at bond 64 (512 x 512 swaps) 214 -> 71 ms, at 128
-// (1024 x 1024) 428 -> 121 ms, 128^3 at 256 (2048 x 2048) 660 -> 202 ms, and
+// components: 256^3 at bond 64 (512 x 512 swaps) 214 -> 55 ms, at 128
+// (1024 x 1024) 428 -> 114 ms, 128^3 at 256 (2048 x 2048) 660 -> 194 ms, 1024^3
+// at 1024 (8192 x 8192) 39.7 -> 14.5 s, and
 // their error against 64 bits halves (8e-14 -> 5e-14, 1.1e-13 -> 6e-14).
 // With l = 2 cap columns and M = Theta^T Theta:
 //   1. Y = orth(Theta^T Omega), then twice Y = orth(M Y); the diagonal of the
@@ -826,8 +827,10 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
 // full SVD.  The rule of Eq. (eps) is taken with the weight outside the l
 // values in every tail, and checked with the discarded weight summed from
 // Theta - X' P' itself.  The full SVD also runs where that check is not clear
-// by 1e-6, where the spectrum is too flat for MAX_FILTER filters, and where a
-// Cholesky pivot breaks down (Theta of rank below l).
+// by 1e-6, where the spectrum is too flat for MAX_FILTER filters, and where the
+// cap lies below the noise level.  Where a Cholesky pivot breaks down (a
+// spectrum that falls by more than about 1e7 over the l columns) the iteration
+// starts again with shifted passes (see STEEP_SHIFT).
 namespace {
 constexpr int PSVD_POWER = 2;     // plain iterations before the filter
 constexpr int MAX_FILTER = 10;    // beyond it the full SVD costs no more
