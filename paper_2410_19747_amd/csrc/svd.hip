@@ -249,44 +249,42 @@ SvdResult svd_oside(const SvdPlan &p, const double *Y, double eps, int cap, int 
     double res[8];
     if (!ok(hipMemcpyAsync(res, b.jb.result, sizeof(res), hipMemcpyDeviceToHost, s))) return out;
     if (!sync()) return out;
-    out.sweeps = (int)fabs(res[7]);
-    if (!(res[7] > 0.0)) {
-      out.err = TTM_ENOCONV;
-      set_last_error("one-sided Jacobi on the %d x %d factor of a %d x %d SVD did not converge in %d sweeps",
-                     p.k, p.k, p.np, p.no, out.sweeps);
-      return out;
-    }
-    if (res[4] != 0.0) {
-      out.err = TTM_ENONFINITE;
-      set_last_error("the singular values of a %d x %d SVD are not finite", p.np, p.no);
-      return out;
-    }
-    out.rank = (int)res[0];
-    out.disc = res[1];
-    out.total = res[2];
-    const int r = out.rank, kg = std::max(r, std::min(p.k, (int)res[6]));
-    if (all) all->kg = kg;
-    if (q.mode == SMALL_RTQ) {
-      double *ucm = (u_layout == SVD_U_T) ? u : b.Xt;
-      double *full = all ? all->u : ucm;
-      const int nc = all ? kg : r;
-      {
+    // Not within max_sweeps sweeps of its own: the block method, whose sweeps
+    // visit the pairs in another order, may need one less.
+    if (res[7] > 0.0) {
+      out.sweeps = (int)res[7];
+      if (res[4] != 0.0) {
+        out.err = TTM_ENONFINITE;
+        set_last_error("the singular values of a %d x %d SVD are not finite", p.np, p.no);
+        return out;
+      }
+      out.rank = (int)res[0];
+      out.disc = res[1];
+      out.total = res[2];
+      const int r = out.rank, kg = std::max(r, std::min(p.k, (int)res[6]));
+      if (all) all->kg = kg;
+      if (q.mode == SMALL_RTQ) {
+        double *ucm = (u_layout == SVD_U_T) ? u : b.Xt;
+        double *full = all ? all->u : ucm;
+        const int nc = all ? kg : r;
+        {
+          Timed tm(timer, KC_JAC_OTHER, s);
+          if (!ok(launch_embed_rows(full, b.jb.W, p.k, p.no, nc, s))) return out;
+        }
+        {
+          Timed tm(timer, KC_QR, s);
+          if (!ok(launch_apply_q(b.S, p.no, p.k, b.Tall, full, nc, b.qr, s))) return out;
+        }
         Timed tm(timer, KC_JAC_OTHER, s);
-        if (!ok(launch_embed_rows(full, b.jb.W, p.k, p.no, nc, s))) return out;
+        if (all && !ok(launch_copy(ucm, all->u, (int64_t)p.no * r, s))) return out;
+        if (u_layout == SVD_U && !ok(launch_transpose(u, ucm, r, p.no, s))) return out;
       }
-      {
-        Timed tm(timer, KC_QR, s);
-        if (!ok(launch_apply_q(b.S, p.no, p.k, b.Tall, full, nc, b.qr, s))) return out;
-      }
-      Timed tm(timer, KC_JAC_OTHER, s);
-      if (all && !ok(launch_copy(ucm, all->u, (int64_t)p.no * r, s))) return out;
-      if (u_layout == SVD_U && !ok(launch_transpose(u, ucm, r, p.no, s))) return out;
+      if (all && sigma_out && !ok(launch_copy(sigma_out, all->sigma, p.k, s))) return out;
+      if (trace)
+        fprintf(stderr, "[ttm] svd %dx%d sweeps=%d rank=%d disc=%.3e total=%.3e\n", p.np, p.no, out.sweeps, out.rank,
+                out.disc, out.total);
+      return out;
     }
-    if (all && sigma_out && !ok(launch_copy(sigma_out, all->sigma, p.k, s))) return out;
-    if (trace)
-      fprintf(stderr, "[ttm] svd %dx%d sweeps=%d rank=%d disc=%.3e total=%.3e\n", p.np, p.no, out.sweeps, out.rank,
-              out.disc, out.total);
-    return out;
   }
   // 1. X = Y^T, its columns in decreasing norm order, ||Y||_F^2
   {

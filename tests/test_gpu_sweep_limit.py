@@ -1,0 +1,45 @@
+"""svd_max_sweeps refuses no product that the block Jacobi method alone
+carries within it: the SVDs in one workgroup, the capped ones and the
+randomized ones, whose sweeps are others, fall back on it.
+
+Tolerance: two truncations of the same products by backward-stable SVDs, 1e-12
+relative (the bound of the parity tests).
+"""
+import pytest
+
+import oracle as O
+import ttm_inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _host(packed):
+    return [c.detach().cpu().numpy() for c in packed.cores()]
+
+
+def _least_limit(T, A, B, chi, tol):
+    """The least svd_max_sweeps at which every SVD of the product converges by
+    the block method alone."""
+    for limit in range(1, 41):
+        try:
+            return limit, T._run("block", A, B, chi, tol, svd_max_sweeps=limit)
+        except T.TTMError as e:
+            assert e.code == T.TTM_ENOCONV
+    raise AssertionError("no limit up to 40")
+
+
+def _check(A, B, chi, tol, what, **opts):
+    import paper_2410_19747_amd as T
+
+    limit, (C0, st0) = _least_limit(T, A, B, chi, tol)
+    print("%s: block method within %d sweeps" % (what, limit), flush=True)
+    C, st = T.multiply(A, B, chi, tol, svd_max_sweeps=limit, **opts)
+    assert st["jacobi_max_sweeps"] <= limit and st["ranks"] == st0["ranks"]
+    return O.rel_frob(_host(C), _host(C0))
+
+
+@pytest.mark.parametrize("phys,ca,cb,chi", [([4] * 6, 16, 16, 16), ([8] * 5, 12, 12, 12),
+                                            ([3, 5, 2, 7, 4, 6, 3], 23, 19, 21)])
+def test_one_workgroup_svds(phys, ca, cb, chi):
+    A, B = I.random_tt(len(phys), phys, ca, 3), I.random_tt(len(phys), phys, cb, 4)
+    assert _check(A, B, chi, 1e-14, "sides up to %d" % (max(phys) * chi)) <= 1e-12
