@@ -1029,6 +1029,11 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
   out.sweeps = so.sweeps;
   out.breakdown = fail != 0;
   if (fail && so.err != TTM_EHIP) return refuse("CholeskyQR breakdown", fail);
+  if (so.err == TTM_ENOCONV || so.err == TTM_ENONFINITE) {
+    // not within max_sweeps, or squares out of range: the full SVD decides
+    clear_last_error();
+    return refuse("no SVD of the projection", so.sweeps);
+  }
   if (so.err != TTM_OK) {
     out.err = so.err;
     return out;

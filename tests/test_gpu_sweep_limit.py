@@ -43,3 +43,10 @@ def _check(A, B, chi, tol, what, **opts):
 def test_one_workgroup_svds(phys, ca, cb, chi):
     A, B = I.random_tt(len(phys), phys, ca, 3), I.random_tt(len(phys), phys, cb, 4)
     assert _check(A, B, chi, 1e-14, "sides up to %d" % (max(phys) * chi)) <= 1e-12
+
+
+@pytest.mark.parametrize("grid,chi", [(64, 32), (64, 64), (128, 40)])
+def test_capped_svds(grid, chi):
+    """Swap matrices of side 8 chi, of which chi triplets are kept."""
+    A, B = I.turbulence_qtt(grid, 101, chi), I.turbulence_qtt(grid, 102, chi)
+    assert _check(A, B, chi, 1e-14, "%d^3 at bond %d" % (grid, chi)) <= 1e-12
