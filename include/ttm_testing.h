@@ -108,6 +108,10 @@ int ttm_test_cholqr2(double *Y, int p, int l, int *breakdown, void *ws, size_t w
 size_t ttm_test_capped_svd_ws_bytes(int m, int n, int cap);
 int ttm_test_capped_svd(const double *Theta, int m, int n, int cap, double eps, double *pt, double *xt, int *rank,
                         int *refused, double *weights, void *ws, size_t ws_bytes, void *stream);
+/* The same within max_sweeps Jacobi sweeps (ttm_test_capped_svd: 60). */
+int ttm_test_capped_svd_sweeps(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt,
+                               double *xt, int *rank, int *refused, double *weights, void *ws, size_t ws_bytes,
+                               void *stream);
 
 #ifdef __cplusplus
 }

@@ -191,6 +191,9 @@ TESTING_PROTOTYPES = {
     "ttm_test_capped_svd": (ctypes.c_int, [_VP, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_double, _VP, _VP,
                                            ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int), F64P, _VP,
                                            ctypes.c_size_t, _VP]),
+    "ttm_test_capped_svd_sweeps": (ctypes.c_int, [_VP, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_double,
+                                                  ctypes.c_int, _VP, _VP, ctypes.POINTER(ctypes.c_int),
+                                                  ctypes.POINTER(ctypes.c_int), F64P, _VP, ctypes.c_size_t, _VP]),
 }
 
 TTM_STATIC_WS_BYTES = 32 << 20

@@ -189,15 +189,17 @@ size_t ttm_test_capped_svd_ws_bytes(int m, int n, int cap) {
   return ttm::svd_ws_doubles(ttm::svd_plan(m, n)) * sizeof(double);
 }
 
-int ttm_test_capped_svd(const double *Theta, int m, int n, int cap, double eps, double *pt, double *xt, int *rank,
-                        int *refused, double *weights, void *ws, size_t ws_bytes, void *stream) {
-  if (!Theta || !pt || !xt || !rank || !refused || !weights || !ws || !(eps >= 0.0)) return TTM_EINVAL;
+int ttm_test_capped_svd_sweeps(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt,
+                               double *xt, int *rank, int *refused, double *weights, void *ws, size_t ws_bytes,
+                               void *stream) {
+  if (!Theta || !pt || !xt || !rank || !refused || !weights || !ws || !(eps >= 0.0) || max_sweeps < 1)
+    return TTM_EINVAL;
   const size_t need = ttm_test_capped_svd_ws_bytes(m, n, cap);
   if (need == 0) return TTM_EUNSUPPORTED;
   if (ws_bytes < need) return TTM_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const ttm::PsvdResult r =
-      ttm::psvd_oside(Theta, m, n, cap, eps, 60, pt, xt, static_cast<double *>(ws), s, nullptr, 0);
+      ttm::psvd_oside(Theta, m, n, cap, eps, max_sweeps, pt, xt, static_cast<double *>(ws), s, nullptr, 0);
   *rank = r.rank;
   *refused = r.fallback ? 1 : 0;
   weights[0] = r.disc;
@@ -205,6 +207,11 @@ int ttm_test_capped_svd(const double *Theta, int m, int n, int cap, double eps, 
   weights[2] = r.missed;
   if (r.err != TTM_OK) return r.err;
   return hipStreamSynchronize(s) == hipSuccess ? TTM_OK : TTM_EHIP;
+}
+
+int ttm_test_capped_svd(const double *Theta, int m, int n, int cap, double eps, double *pt, double *xt, int *rank,
+                        int *refused, double *weights, void *ws, size_t ws_bytes, void *stream) {
+  return ttm_test_capped_svd_sweeps(Theta, m, n, cap, eps, 60, pt, xt, rank, refused, weights, ws, ws_bytes, stream);
 }
 
 }  // extern "C"
