@@ -888,7 +888,7 @@ bool psvd_eligible(int m, int n, int cap) {
 
 namespace {
 PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
-                    double *ws, hipStream_t s, KernelTimer *timer, int trace, bool steep) {
+                    double *ws, hipStream_t s, KernelTimer *timer, int trace, double *sigma, bool steep) {
   PsvdResult out;
   const int l = rsvd_sketch_cols(cap);
   const int64_t part = psvd_part_doubles(m, n, cap);
@@ -1094,6 +1094,7 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
   if (!(sr > 100.0 * 8.0 * sqrt(k) * kU * sqrt(tot))) return refuse("kept values near the noise level", sr);
   if (r > 1 && !(disc + sr * sr >= cut * (1.0 + 1e-6))) return refuse("the rule is not sure at the rank", disc / tot);
   if (r < cap && !(disc < cut * (1.0 - 1e-6))) return refuse("the rule is not sure below the cap", disc / tot);
+  if (sigma && !ok(launch_copy(sigma, b.diag, r, s))) return out;
   out.rank = r;
   out.disc = disc;
   out.total = tot;
@@ -1106,10 +1107,10 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
 }  // namespace
 
 PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
-                      double *ws, hipStream_t s, KernelTimer *timer, int trace) {
-  PsvdResult out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, false);
+                      double *ws, hipStream_t s, KernelTimer *timer, int trace, double *sigma) {
+  PsvdResult out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, sigma, false);
   if (out.breakdown && out.err == TTM_OK)
-    out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, true);
+    out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, sigma, true);
   return out;
 }
 

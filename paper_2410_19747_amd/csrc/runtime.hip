@@ -624,10 +624,11 @@ struct Runner {
   // ---- the cap leading triplets of a swap matrix (psvd_oside) with the same
   // bookkeeping as svd(), which counts them as the full SVD they stand for.
   // *done = false when it was refused and the full SVD must run.
-  int psvd(const SvdPlan &sp, const double *Y, int cap, double *pt, double *xt, double *ws, bool *done) {
+  int psvd(const SvdPlan &sp, const double *Y, int cap, double *pt, double *xt, double *ws, bool *done,
+           double *sigma) {
     *done = false;
     const int m = sp.np, n = sp.no;
-    PsvdResult ps = psvd_oside(Y, m, n, cap, eps_, o.svd_max_sweeps, pt, xt, ws, st, &timer, trace);
+    PsvdResult ps = psvd_oside(Y, m, n, cap, eps_, o.svd_max_sweeps, pt, xt, ws, st, &timer, trace, sigma);
     jac_sweeps += ps.sweeps;
     jac_max = std::max(jac_max, ps.sweeps);
     if (ps.err != TTM_OK) {
@@ -710,22 +711,13 @@ struct Runner {
     }
     bool have_x = false;
     if (!done && o.svd_mode == TTM_SVD_JACOBI && !o.forced && !o.block_svd && psvd_eligible(m, n, cap)) {
-      r = psvd(sp, Y, cap, pn, xn, sws, &done);
+      r = psvd(sp, Y, cap, pn, xn, sws, &done, tape ? e.sigma : nullptr);
       if (r < 0) return;
       have_x = done;
       if (done && tape) {
-        // the reverse mode needs the other vectors too: the full SVD, with
-        // these r in the place of its own
-        double *other = take();
-        if (!other) return;
-        const SvdResult so = svd_oside(sp, Y, eps_, cap, r, o.svd_max_sweeps, other, SVD_U_T, nullptr, sws, st, &timer,
-                                       trace, &all);
-        give(other);
-        if (so.err != TTM_OK) {
-          if (err == TTM_OK) err = so.err;
-          return;
-        }
-        if (!hip(launch_copy(all.u, pn, (int64_t)n * r, st))) return;
+        e.capped = true;
+        all.kg = r;
+        if (!hip(launch_copy(e.V, pn, (int64_t)n * r, st))) return;
       }
     }
     if (!done) r = svd(sp, Y, sws, cap, pn, SVD_U_T, tape ? &all : nullptr);

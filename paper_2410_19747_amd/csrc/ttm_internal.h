@@ -350,7 +350,8 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
 
 // The cap leading singular triplets of a swap matrix at full accuracy
 // (rsvd.hip): as svd_oside with u = P' = V_r^T (pt, r x n row-major), and
-// X' = Theta V_r (xt, m x r row-major) besides.  fallback = true (no error)
+// X' = Theta V_r (xt, m x r row-major) besides; sigma (optional, device): the r
+// values, decreasing.  fallback = true (no error)
 // where the result was refused: the caller runs svd_oside in the same
 // workspace, whose size (svd_ws_doubles of the full SVD) is enough here.
 struct PsvdResult {
@@ -364,7 +365,7 @@ struct PsvdResult {
 };
 bool psvd_eligible(int m, int n, int cap);
 PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
-                      double *ws, hipStream_t s, KernelTimer *timer, int trace);
+                      double *ws, hipStream_t s, KernelTimer *timer, int trace, double *sigma = nullptr);
 
 // ------------------------------------------------------------------ reverse mode
 // The record a TTM product keeps for its reverse mode: one entry per step,
@@ -382,12 +383,14 @@ struct TapeEntry {
   // CONTRACT: K [dl, d, dm], X [dm, d, dr].
   // SWAP: P [dl, dp, dm], X [dm, dx, dr]; theta (m = dl dx by n = dp dr,
   // column-major); V (n x kg, column-major) the resolved right singular
-  // vectors, sigma (min(m, n), decreasing); Z = theta V_r (m x r, row-major).
+  // vectors, sigma (min(m, n), decreasing); Z = theta V_r (m x r, row-major);
+  // capped: V and sigma of the r kept triplets alone (kg = r), with room for all.
   // ROUND: M = Pi_i (m = rl d by n = rr, row-major); V (m x kg, column-major)
   // its resolved left singular vectors; sigma; Zt = S_r V_r^T (r x n); nxt
   // (n x ncol) the old next core.
   int m = 0, n = 0, k = 0, ncol = 0, r = 0, kg = 0;
   int rl = 0, d = 0, dl = 0, dp = 0, dm = 0, dx = 0, dr = 0;
+  bool capped = false;
   double *M = nullptr, *Q = nullptr, *R = nullptr, *nxt = nullptr;
   double *K = nullptr, *X = nullptr, *P = nullptr, *theta = nullptr, *V = nullptr, *sigma = nullptr,
          *Z = nullptr, *Zt = nullptr;

@@ -16,6 +16,8 @@
 //     so they contribute nothing);
 //     Theta_bar = (Z_bar + Theta Y) V_r^T + Z Y^T with
 //     Y = V_d [F o (V_d^T V_r_bar)] + (I - V V^T) V_r_bar S_r^{-2};
+//     where the swap computed the kept triplets alone (psvd_oside), Y is the
+//     same by a series of the deflated matrix (capped_adjoint);
 //   * the leg-exchange merge: two products after a permutation;
 //   * the final rounding sweep: the same SVD adjoint on Pi_i^T.
 // The ranks are those of the recorded forward pass (piecewise constant).
@@ -30,6 +32,8 @@ namespace ttm {
 namespace {
 
 constexpr int NT = 256;
+constexpr double LOG_VANISHED = 39.5;  // a power of E below exp(-39.5) = 2^-57 adds nothing
+constexpr int MAX_DOUBLINGS = 42;      // ends for relative gaps above about 1e-11
 
 int grid_for(int64_t n) {
   int64_t g = (n + NT - 1) / NT;
@@ -74,6 +78,31 @@ __global__ void null_add_kernel(double *__restrict__ Y, const double *__restrict
     const int t = (int)(x / n);
     const double l = sig[t] * sig[t];
     if (l > 0.0) Y[x] += N[x] / l;
+  }
+}
+
+// x /= *v.
+__global__ void divide_kernel(double *__restrict__ x, int64_t n, const double *__restrict__ v) {
+  const double d = v[0];
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x)
+    x[q] /= d;
+}
+
+// X[j + t n] += (s_{r-1} / s_t)^(2 p) T[j + t n], j < n, t < r.
+__global__ void series_add_kernel(double *__restrict__ X, const double *__restrict__ T,
+                                  const double *__restrict__ sig, int n, int r, double p) {
+  const int64_t total = (int64_t)n * r;
+  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total; x += (int64_t)gridDim.x * blockDim.x)
+    X[x] = fma(pow(sig[r - 1] / sig[x / n], 2.0 * p), T[x], X[x]);
+}
+
+// X[j + t n] /= s_t^2, or with B: X = (B + (s_{r-1} / s_t)^2 X) / s_t^2.
+__global__ void series_end_kernel(double *__restrict__ X, const double *__restrict__ B,
+                                  const double *__restrict__ sig, int n, int r) {
+  const int64_t total = (int64_t)n * r;
+  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total; x += (int64_t)gridDim.x * blockDim.x) {
+    const double s = sig[x / n], q = sig[r - 1] / s;
+    X[x] = (B ? fma(q * q, X[x], B[x]) : X[x]) / (s * s);
   }
 }
 
@@ -130,6 +159,7 @@ struct Back {
   int err = TTM_OK;
   double *S[8] = {};  // scratch, each `scap` doubles
   size_t scap = 0;
+  double *svd_ws = nullptr;  // the product's workspace, done with by now
   bool ok(hipError_t e, const char *what) {
     if (e != hipSuccess) {
       if (err == TTM_OK) {
@@ -150,9 +180,17 @@ struct Back {
   // column-major resolved right singular vectors; sig: k values, decreasing.
   bool svd_adjoint(const double *mat, int m, int n, const double *V, const double *sig, int r, int kg,
                    const double *Z, int64_t zs_r, int64_t zs_c, const double *Zb, double *Vrb, double *matbar) {
+    return add_z(mat, m, n, r, Zb, Vrb) &&
+           resolved_adjoint(mat, m, n, V, sig, r, kg, Z, zs_r, zs_c, Zb, Vrb, matbar);
+  }
+  // V_r_bar += mat^T Z_bar  (the dependence of Z on V_r)
+  bool add_z(const double *mat, int m, int n, int r, const double *Zb, double *Vrb) {
+    return mm(gemm(n, r, m, mat, m, 1, Zb, r, 1, Vrb, 1, n, 1.0, 1.0));
+  }
+  bool resolved_adjoint(const double *mat, int m, int n, const double *V, const double *sig, int r, int kg,
+                        const double *Z, int64_t zs_r, int64_t zs_c, const double *Zb, const double *Vrb,
+                        double *matbar) {
     double *Mm = S[2], *Y = S[3], *Nb = S[4], *G1 = S[5], *T1 = S[6];
-    // V_r_bar += mat^T Z_bar  (the dependence of Z on V_r)
-    if (!mm(gemm(n, r, m, mat, m, 1, Zb, r, 1, Vrb, 1, n, 1.0, 1.0))) return false;
     // Y = V_d [F o (V_d^T V_r_bar)] over the resolved dropped vectors
     const int kd = kg - r;
     if (kd > 0) {
@@ -171,6 +209,10 @@ struct Back {
       hipLaunchKernelGGL(null_add_kernel, dim3(grid_for((int64_t)n * r)), dim3(NT), 0, st, Y, Nb, sig, n, r);
       if (!ok(hipGetLastError(), "the null-space weights of an SVD adjoint")) return false;
     }
+    return finish_adjoint(mat, m, n, V, r, Z, zs_r, zs_c, Zb, Y, T1, matbar);
+  }
+  bool finish_adjoint(const double *mat, int m, int n, const double *V, int r, const double *Z, int64_t zs_r,
+                      int64_t zs_c, const double *Zb, const double *Y, double *T1, double *matbar) {
     // T1 = Z_bar + mat Y (m x r, row-major)
     if (!copy(T1, Zb, (int64_t)m * r)) return false;
     if (!mm(gemm(m, r, n, mat, 1, m, Y, 1, n, T1, r, 1, 1.0, 1.0))) return false;
@@ -180,6 +222,100 @@ struct Back {
     return true;
   }
 
+  // The same for a swap of which only the r kept triplets are known (V: n x r,
+  // sig: r values, Z row-major).  With D = mat - Z V_r^T, the dropped part, and
+  // B = (I - V_r V_r^T) V_r_bar, column t of Y solves
+  // (s_t^2 - D^T D) y = b, so that it is the sum of (D^T D)^k b / s_t^(2k + 2),
+  // taken by doubling: with D over s_r, E = D^T D below 1 in norm and
+  // q_t = (s_r / s_t)^2, X = B and then
+  //   X <- X + E^(2^j) X diag(q_t^(2^j)),  E^(2^(j+1)) = (E^(2^j))^2
+  // until E's power has vanished (log2 of about 40 over the relative gap at
+  // the cut), Y = X diag(1 / s_t^2).  On the shorter side of mat: for m < n,
+  // E = D D^T, X = D B, Y = (B + D^T X diag(q_t)) diag(1 / s_t^2).  D is formed
+  // before its Gram, so that the rounding of s_1^2 does not meet s_{r+1}^2.
+  // Bound by the squarings.  The Jacobi SVD of mat for its dropped vectors takes
+  // 19 ms at 1024 x 1024 and 7.9 at 512 x 512: with it ttm_multiply_vjp of two
+  // 256^3 fields took 507 ms at bond 128 and 249 at 64, so 163 and 76.  The
+  // errors are those of the SVD's vectors (at s_r / s_1 from 0.3 to 1e-8 and
+  // gaps from 0.5 to 1e-7, either within a factor of three of the other).
+  // Where the series does not end (a tie at the cut, but for rounding), that
+  // SVD it is, with the kept vectors as they are.
+  bool capped_adjoint(const TapeEntry &t, const double *Zb, double *Vrb, double *matbar) {
+    const double *mat = t.theta, *Z = t.Z, *sig = t.sigma;
+    const int m = t.m, n = t.n, r = t.r, side = std::min(m, n);
+    const bool wide = m < n;
+    double *V = t.V, *D = matbar, *E = S[2], *E2 = S[3], *X = S[4], *T = S[5], *G = S[6], *B = S[7];
+    if (!add_z(mat, m, n, r, Zb, Vrb)) return false;
+    if (!mm(gemm(r, r, n, V, n, 1, Vrb, 1, n, G, 1, r)) || !copy(B, Vrb, (int64_t)n * r) ||
+        !mm(gemm(n, r, r, V, 1, n, G, 1, r, B, 1, n, -1.0, 1.0)))
+      return false;
+    if (!copy(D, mat, (int64_t)m * n) || !mm(gemm(m, n, r, Z, r, 1, V, n, 1, D, 1, m, -1.0, 1.0))) return false;
+    hipLaunchKernelGGL(divide_kernel, dim3(grid_for((int64_t)m * n)), dim3(NT), 0, st, D, (int64_t)m * n, sig + r - 1);
+    if (!ok(hipGetLastError(), "the scaling of a dropped part")) return false;
+    if (wide) {
+      if (!mm(gemm(m, m, n, D, 1, m, D, m, 1, E, 1, m)) || !mm(gemm(m, r, n, D, 1, m, B, 1, n, X, 1, m))) return false;
+    } else {
+      if (!mm(gemm(n, n, m, D, m, 1, D, 1, m, E, 1, n)) || !copy(X, B, (int64_t)n * r)) return false;
+    }
+    int left = -1;  // doublings still due, once known
+    for (int j = 0; left != 0; ++j) {
+      if (left < 0 && j % 3 == 0) {
+        double f = 0.0;  // ||E||_F^2, no less than ||E||_2^2
+        if (!ok(launch_column_norms(E, side, side, G, st), "the norms of a dropped part") ||
+            !ok(launch_frob_from_norms(G, side, G + side, st), "the norm of a dropped part") ||
+            !ok(hipMemcpyAsync(&f, G + side + 5, sizeof(f), hipMemcpyDeviceToHost, st), "a read-back") ||
+            !ok(hipStreamSynchronize(st), "a synchronisation of the reverse mode"))
+          return false;
+        if (f < 0.5) left = f > 0.0 ? std::max(0, (int)ceil(log2(2.0 * LOG_VANISHED / -log(f)))) : 0;
+        if (left == 0) break;
+        if (j >= MAX_DOUBLINGS || !(f < 1e12)) return full_adjoint(t, Zb, Vrb, matbar);
+      }
+      if (!mm(gemm(side, r, side, E, 1, side, X, 1, side, T, 1, side))) return false;
+      hipLaunchKernelGGL(series_add_kernel, dim3(grid_for((int64_t)side * r)), dim3(NT), 0, st, X, T, sig, side, r,
+                         ldexp(1.0, j));
+      if (!ok(hipGetLastError(), "a doubling of the reverse mode")) return false;
+      if (left != 1 && !mm(gemm(side, side, side, E, 1, side, E, 1, side, E2, 1, side))) return false;
+      std::swap(E, E2);
+      if (left > 0) --left;
+    }
+    double *Y = X;
+    if (wide) {
+      Y = G;
+      G = X;
+      if (!mm(gemm(n, r, m, D, m, 1, X, 1, m, Y, 1, n))) return false;
+    }
+    hipLaunchKernelGGL(series_end_kernel, dim3(grid_for((int64_t)n * r)), dim3(NT), 0, st, Y, wide ? B : nullptr, sig,
+                       n, r);
+    if (!ok(hipGetLastError(), "the weights of a capped swap's adjoint")) return false;
+    // what rounding left of Y along the kept vectors
+    if (!mm(gemm(r, r, n, V, n, 1, Y, 1, n, G, 1, r)) || !mm(gemm(n, r, r, V, 1, n, G, 1, r, Y, 1, n, -1.0, 1.0)))
+      return false;
+    return finish_adjoint(mat, m, n, V, r, Z, r, 1, Zb, Y, T, matbar);
+  }
+  // ... with every vector by the full SVD (within the default sweep limit: the
+  // caller's is for the product), the dropped ones made orthogonal to the kept
+  // ones, which stay.
+  bool full_adjoint(const TapeEntry &t, const double *Zb, const double *Vrb, double *matbar) {
+    const int m = t.m, n = t.n, r = t.r;
+    double *V = t.V, *u = S[4], *G = S[6], *kept = S[7];
+    SvdAll all;
+    all.u = V;
+    all.sigma = t.sigma;
+    if (!copy(kept, V, (int64_t)n * r)) return false;
+    const SvdResult so = svd_oside(svd_plan(m, n), t.theta, 0.0, r, r, 40, u, SVD_U_T, nullptr, svd_ws, st,
+                                   nullptr, 0, &all);
+    if (so.err != TTM_OK) {
+      if (err == TTM_OK) err = so.err;
+      return false;
+    }
+    const int kd = all.kg - r;
+    double *dropped = V + (int64_t)r * n;
+    if (!copy(V, kept, (int64_t)n * r)) return false;
+    if (kd > 0 && (!mm(gemm(r, kd, n, V, n, 1, dropped, 1, n, G, 1, r)) ||
+                   !mm(gemm(n, kd, r, V, 1, n, G, 1, r, dropped, 1, n, -1.0, 1.0))))
+      return false;
+    return resolved_adjoint(t.theta, m, n, V, t.sigma, r, all.kg, t.Z, r, 1, Zb, Vrb, matbar);
+  }
   // Cotangent of a QR-moved core: M (m x n row-major) = Q R, the next core
   // became R nxt (nxt: n x ncol).  In: Qb (m x k, the cotangent of the new
   // core), nb (k x ncol, of the new next core).  Out: Mb (m x n) and nxtb
@@ -283,6 +419,7 @@ int run_vjp(const ttm_tt *A, const ttm_tt *B, int chi_out, double tol, const ttm
   char *xbase = sbase + L.slots;
   for (int i = 0; i < 8; ++i) bk.S[i] = reinterpret_cast<double *>(xbase + (size_t)i * al((size_t)L.sc * 8));
   bk.scap = (size_t)L.sc;
+  bk.svd_ws = static_cast<double *>(ws);
   size_t next = 0;
   auto slot = [&](int rl, int d, int rr) {
     Slot s;
@@ -327,7 +464,9 @@ int run_vjp(const ttm_tt *A, const ttm_tt *B, int chi_out, double tol, const ttm
       double *thb = bk.S[0], *Vrb = bk.S[1], *T = bk.S[7];
       // the cotangent of P' = V_r^T (r x nn, row-major) is V_r_bar as nn x r column-major
       if (!bk.copy(Vrb, Pib[t.p].p, (int64_t)r * nn)) break;
-      if (!bk.svd_adjoint(t.theta, m, nn, t.V, t.sigma, r, t.kg, t.Z, r, 1, Xb.p, Vrb, thb)) break;
+      if (!(t.capped ? bk.capped_adjoint(t, Xb.p, Vrb, thb)
+                     : bk.svd_adjoint(t.theta, m, nn, t.V, t.sigma, r, t.kg, t.Z, r, 1, Xb.p, Vrb, thb)))
+        break;
       hipLaunchKernelGGL(legs_back_kernel, dim3(grid_for((int64_t)m * nn)), dim3(NT), 0, st, thb, t.dl, t.dp, t.dx,
                          t.dr, T);
       if (!bk.ok(hipGetLastError(), "the leg exchange of the reverse mode")) break;
