@@ -85,6 +85,16 @@ __global__ void diag_kernel(const double *__restrict__ G, int ld, int n, double 
   if (i < n) dst[i] = G[(int64_t)i * ld + i];
 }
 
+// dst[i] = the i-th Cholesky pivot over the squared norm gd[i] of its column,
+// from the inverses of R's diagonal blocks; 1 where the pivot broke down.
+__global__ void pivot_kernel(const double *__restrict__ rinv, const double *__restrict__ gd, int n,
+                             double *__restrict__ dst) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double x = rinv[((int64_t)(i / CNB) * CNB + i % CNB) * CNB + i % CNB];
+  dst[i] = 1.0 / (x * x * gd[i]);
+}
+
 // 1 / sqrt(d) for d > 0: the hardware estimate (about 2^-24 off) and one step
 // of third order.
 __device__ __forceinline__ double rsqrt_nr(double d) {
@@ -845,6 +855,23 @@ constexpr int MAX_FILTER = 10;    // beyond it the full SVD costs no more
 // 512 (4096 x 4096: 3646 -> 1838 ms).
 constexpr double STEEP_SHIFT = 1e-12;
 
+// Whether the cap lies below noise (of the largest value) in a spectrum whose
+// sketch of l columns breaks a CholeskyQR down, by the pivots (over their
+// columns' norms, 1 where they broke) of the start: the first r0 < cap stand,
+// falling as sigma^2 does.  Either they fall at a rate that takes them below
+// noise^2 by the cap, or the last of them stands four digits above the level of
+// breakdown, so that the values end there.  The shifted passes would then end
+// in a refusal by the noise level: products of rank 9 and 16 at caps 40 and 64
+// (6 sites of 8) took 31.5 and 39 ms with them, 23.4 and 34 without.
+bool cap_in_noise(const std::vector<double> &pivots, int cap, double noise) {
+  constexpr double LEVEL = 64.0 * kU;
+  int r0 = 1;
+  while (r0 < (int)pivots.size() && pivots[r0] < 1.0 - 1e-9) ++r0;
+  if (r0 >= cap) return false;
+  const double last = pivots[r0 - 1];
+  return last > 1e4 * LEVEL || pow(last, (double)cap / r0) < noise * noise;
+}
+
 struct PsvdBufs {
   double *Y, *W, *Z, *T, *vt, *small, *full, *diag;
   int *fail;
@@ -984,6 +1011,10 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
     if (!sumsq(Theta, (int64_t)m * n, b.full)) return out;
   }
   if (!prod(true, zcur, ycur) || !orth(ycur, n)) return out;
+  if (!steep) {
+    hipLaunchKernelGGL(pivot_kernel, dim3((l + 255) / 256), dim3(256), 0, s, b.cq.rinv, b.cq.gd, l, b.vt);
+    if (!ok(hipGetLastError())) return out;
+  }
   for (int it = 0; it < PSVD_POWER; ++it) {
     const bool last = it + 1 == PSVD_POWER;
     if (!prod(false, ycur, zcur) || (steep && !orth(zcur, m))) return out;
@@ -996,14 +1027,23 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
   if (!ok(hipMemcpyAsync(&tot, b.full, sizeof(double), hipMemcpyDeviceToHost, s))) return out;
   if (!ok(hipMemcpyAsync(&fail, b.fail, sizeof(int), hipMemcpyDeviceToHost, s))) return out;
   if (!sync()) return out;
+  // the level below which the full SVD decides, with room
+  const double noise = 100.0 * 8.0 * sqrt((double)std::min(m, n)) * kU;
   out.breakdown = fail != 0;
+  if (fail && !steep) {
+    if (!ok(hipMemcpyAsync(h.data(), b.vt, sizeof(double) * l, hipMemcpyDeviceToHost, s))) return out;
+    if (!sync()) return out;
+    if (cap_in_noise(h, cap, noise)) {
+      out.breakdown = false;
+      return refuse("the cap lies in the noise", h[0]);
+    }
+  }
   if (fail) return refuse("CholeskyQR breakdown", fail);
   if (steep)  // of Theta^T Z, not of M Y
     for (double &x : h) x *= x;
   std::sort(h.begin(), h.end(), [](double x, double y) { return x > y; });
   const double bnd = h[l - 1], kept = h[cap - 1];
   // the shift hides where the spectrum ends: that the full SVD decides
-  const double noise = 100.0 * 8.0 * sqrt((double)std::min(m, n)) * kU;
   if (steep && !(kept > noise * noise * tot)) return refuse("the cap lies in the noise", kept / tot);
   // 2. the filter: each raises the cap-th direction over the rest by
   // 2 x^2 - 1; the start has raised it by (kept / bnd)^(power + 1/2).  What
