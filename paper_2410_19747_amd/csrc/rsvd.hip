@@ -1054,11 +1054,16 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
   const double need = log(1e18) + 0.5 * log(kept / tot) - (PSVD_POWER + 0.5) * log(kept / bnd);
   const int filters = std::max(0, (int)ceil(need / log(gain)));
   if (filters > MAX_FILTER) return refuse("too flat", filters);
+  // M over 4^e, near ||Theta||_F^2: y is of fourth order in Theta and its Gram of
+  // eighth, out of range for a norm beyond 1e38 or below 1e-38 (a power of two:
+  // the same digits)
+  const int e = ilogb(sqrt(tot));
+  const double down = ldexp(1.0, -e), b1 = ldexp(bnd, -2 * e);
   for (int it = 0; it < filters; ++it) {
     // w = M y - b y, y <- M w + (b^2 / 8) y = (b^2 / 8) T_2((2 / b) M - I) y
     if (!ok(launch_copy(wcur, ycur, (int64_t)n * l, s))) return out;
-    if (!prod(false, ycur, zcur) || !prod(true, zcur, wcur, 1.0, -bnd)) return out;
-    if (!prod(false, wcur, zcur) || !prod(true, zcur, ycur, 1.0, 0.125 * bnd * bnd)) return out;
+    if (!prod(false, ycur, zcur, down) || !prod(true, zcur, wcur, down, -b1)) return out;
+    if (!prod(false, wcur, zcur, down) || !prod(true, zcur, ycur, down, 0.125 * b1 * b1)) return out;
     if (!orth(ycur, n)) return out;
   }
   // 3. Z = orth(Theta Y), the SVD of Theta^T Z

@@ -42,3 +42,18 @@ def test_low_rank_costs_one_start(rank, chi, cap):
     assert count(st) <= count(full) + 8 * st["n_swap"]
     assert max(C.bonds) == rank ** 2
     assert O.rel_frob(_host(C), O.ttm(A, B, cap, 0.0).cores) <= 1e-12
+
+
+@pytest.mark.parametrize("scale", [1e-70, 1e-45, 1e45, 1e70])
+def test_scale_does_not_refuse(scale):
+    """The capped SVD of the matrix times a power of two: the same vectors to
+    the bit, where the squares of its squares stay in range."""
+    import test_gpu_svd_capped as S
+
+    scale = 2.0 ** round(np.log2(scale))
+    m, n, cap = 200, 260, 32
+    M = S._with_values(m, n, (1.0 + np.arange(200)) ** -1.2, 9)[0]
+    a, b = S._capped(M, cap, 1e-14), S._capped(M * scale, cap, 1e-14)
+    assert a is not None and b is not None
+    assert a[2] == b[2] == cap
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1] * scale, b[1])
