@@ -158,10 +158,11 @@ enum { TTM_PREC_F64 = 0, TTM_PREC_F32 = 1, TTM_PREC_BF16 = 2, TTM_PREC_BF16X3 = 
 /* Kernel classes of ttm_stats.kernel_ms / kernel_launches. */
 enum {
   TTM_KC_GEMM = 0,         /* contractions, merges, R and S V^T products          */
-  TTM_KC_QR = 1,           /* Householder QR: gauge moves and the SVDs' preconditioner */
+  TTM_KC_QR = 1,           /* QR: gauge moves, the SVDs' preconditioner, CholeskyQR */
   TTM_KC_JAC_GRAM = 2,     /* Jacobi SVD: partial Gram matrices of block pairs     */
   TTM_KC_JAC_SOLVE = 3,    /* Jacobi SVD: diagonalisation of each block-pair Gram  */
-  TTM_KC_JAC_OTHER = 4,    /* SVD: ordering, R^T, convergence, norms, sort, write  */
+  TTM_KC_JAC_OTHER = 4,    /* SVD: ordering, R^T, convergence, norms, sort, write; a whole
+                              SVD by one workgroup */
   TTM_KC_OTHER = 5,        /* copies, reversal, transposes, checks                 */
   TTM_KC_JAC_APPLY = 6,    /* Jacobi SVD: rotation of the column blocks            */
   TTM_KC_COUNT = 7
@@ -175,16 +176,20 @@ typedef struct ttm_stats {
   int32_t n_qr;            /* QR gauge moves, including input canonicalisation */
   int32_t n_svd;           /* truncating SVDs (swaps + final sweep)            */
   int32_t n_trace;         /* entries written to the traces                    */
-  int32_t sweeps;          /* conventional: sweeps run; TTM: total Jacobi sweeps */
+  int32_t sweeps;          /* conventional: sweeps run; TTM: total Jacobi sweeps (of a block
+                              method or of one workgroup; not the passes over neighbours) */
   int32_t jacobi_max_sweeps; /* most Jacobi sweeps any one SVD needed          */
   double discarded_sq_sum; /* sum over SVDs of the discarded weight            */
   double error_bound;      /* sum over SVDs of sqrt(discarded weight): bounds ||C - A*B|| */
-  double model_flops;      /* algorithmic flops of the recorded schedule       */
+  double model_flops;      /* algorithmic flops of the recorded schedule, each SVD's by the
+                              method whose result was taken: full ones (of either kind) by the
+                              bidiagonalisation model, capped and randomized ones by their steps */
   double svd_model_flops;  /* the part of model_flops spent in SVDs            */
   double jacobi_solve_flops; /* arithmetic of the Jacobi pair solves themselves (Gram
                               partial sums, the in-LDS rotation sweep, the
                               re-orthogonalisation), counted for every pair
-                              launched: the solve kernel's own work       */
+                              launched: the solve kernel's own work, none for
+                              SVDs by one workgroup */
   size_t peak_ws_bytes;    /* workspace bytes the call used                    */
   double kernel_ms[TTM_KC_COUNT];        /* with opt.profile: summed event time per class */
   int64_t kernel_launches[TTM_KC_COUNT]; /* with opt.profile: timed regions per class: one launch

@@ -753,6 +753,7 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
     so = svd_oside(sp, Ysvd, eps, cap, 0, max_sweeps, b.vbt, SVD_U_T, b.sig, b.svd, s, timer, trace, nullptr, b.full);
   }
   out.sweeps = so.sweeps;
+  out.solve_flops = so.solve_flops;
   if (so.err != TTM_OK) {
     out.err = so.err;
     return out;
@@ -1072,6 +1073,7 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
   if (!ok(hipMemcpyAsync(&fail, b.fail, sizeof(int), hipMemcpyDeviceToHost, s))) return out;
   SvdResult so = svd_columns(ycur, wcur, n, l, eps, cap, max_sweeps, pt, b.diag, b.svd, s, timer, trace, b.full);
   out.sweeps = so.sweeps;
+  out.solve_flops = so.solve_flops;
   out.breakdown = fail != 0;
   if (fail && so.err != TTM_EHIP) return refuse("CholeskyQR breakdown", fail);
   if (so.err == TTM_ENOCONV || so.err == TTM_ENONFINITE) {
@@ -1144,6 +1146,15 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
   out.disc = disc;
   out.total = tot;
   out.filters = filters;
+  // products, orthonormalisations (Gram, Cholesky and inverse, solve; three
+  // passes and half steps besides when steep), the SVD of the projection (the
+  // bidiagonalisation model), and the checks
+  const double ld = l, md = m, nd = n, starts = 1.0 + PSVD_POWER, passes = steep ? 3.0 : 1.0;
+  auto orth_flops = [&](double p) { return passes * (2.0 * p * ld * ld + 2.0 / 3.0 * ld * ld * ld); };
+  out.flops = 2.0 * md * nd * ld * (1.0 + 2.0 * PSVD_POWER + 4.0 * filters + 2.0) +
+              (starts + filters) * orth_flops(nd) + (2.0 + (steep ? PSVD_POWER : 0)) * orth_flops(md) +
+              4.0 * nd * ld * ld - (4.0 / 3.0) * ld * ld * ld + 4.0 * (nd + ld) * ld * r + 4.0 * md * nd * r +
+              4.0 * md * ld * r;
   if (trace)
     fprintf(stderr, "[ttm] psvd %dx%d l=%d filters=%d sweeps=%d rank=%d missed=%.2e disc=%.3e total=%.3e\n", m, n, l,
             filters, out.sweeps, r, out.missed, disc, tot);
@@ -1154,8 +1165,11 @@ PsvdResult psvd_run(const double *Theta, int m, int n, int cap, double eps, int 
 PsvdResult psvd_oside(const double *Theta, int m, int n, int cap, double eps, int max_sweeps, double *pt, double *xt,
                       double *ws, hipStream_t s, KernelTimer *timer, int trace, double *sigma) {
   PsvdResult out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, sigma, false);
-  if (out.breakdown && out.err == TTM_OK)
+  if (out.breakdown && out.err == TTM_OK) {
+    const double before = out.solve_flops;
     out = psvd_run(Theta, m, n, cap, eps, max_sweeps, pt, xt, ws, s, timer, trace, sigma, true);
+    out.solve_flops += before;
+  }
   return out;
 }
 

@@ -560,6 +560,7 @@ struct Runner {
                              trace, all);
     jac_sweeps += so.sweeps;
     jac_max = std::max(jac_max, so.sweeps);
+    solve_flops += so.solve_flops;
     if (so.err != TTM_OK) {
       if (err == TTM_OK) err = so.err;
       return -1;
@@ -576,15 +577,6 @@ struct Runner {
     const double f = 4.0 * m * (double)n * n - (4.0 / 3.0) * n * (double)n * n + 4.0 * (m + n) * (double)n * so.rank;
     flops += f;
     svd_flops += f;
-    // the solve kernel's own arithmetic per pair and launch: the sum of gsw
-    // partial Grams, B2 - 1 rotation steps (6 flops per entry of G and Q),
-    // and two B2^3 products of the re-orthogonalisation
-    {
-      const JacobiPlan &jp = sp.jp;
-      const double b2 = 2.0 * jp.bw;
-      const double per_pair = jp.gsw * b2 * b2 + 6.0 * b2 * b2 * (b2 - 1.0) + 4.0 * b2 * b2 * b2;
-      solve_flops += (double)so.sweeps * jp.rounds * jp.pairs * per_pair;
-    }
     return so.rank;
   }
 
@@ -597,6 +589,7 @@ struct Runner {
                                o.seed, (int64_t)n_rsvd << 40, pt, ws, st, &timer, trace);
     ++n_rsvd;
     jac_sweeps += rs.sweeps;
+    solve_flops += rs.solve_flops;
     jac_max = std::max(jac_max, rs.sweeps);
     if (rs.err != TTM_OK) {
       if (err == TTM_OK) err = rs.err;
@@ -622,14 +615,15 @@ struct Runner {
   }
 
   // ---- the cap leading triplets of a swap matrix (psvd_oside) with the same
-  // bookkeeping as svd(), which counts them as the full SVD they stand for.
-  // *done = false when it was refused and the full SVD must run.
+  // bookkeeping as svd(), the flops those of its own steps; sigma (or null): the
+  // r values.  *done = false when it was refused and the full SVD must run.
   int psvd(const SvdPlan &sp, const double *Y, int cap, double *pt, double *xt, double *ws, bool *done,
            double *sigma) {
     *done = false;
     const int m = sp.np, n = sp.no;
     PsvdResult ps = psvd_oside(Y, m, n, cap, eps_, o.svd_max_sweeps, pt, xt, ws, st, &timer, trace, sigma);
     jac_sweeps += ps.sweeps;
+    solve_flops += ps.solve_flops;
     jac_max = std::max(jac_max, ps.sweeps);
     if (ps.err != TTM_OK) {
       if (err == TTM_OK) err = ps.err;
@@ -645,10 +639,8 @@ struct Runner {
       o.discard_trace[n_trace] = ps.disc;
     }
     ++n_trace;
-    const double mx = std::max(m, n), k = std::min(m, n);
-    const double f = 4.0 * mx * k * k - (4.0 / 3.0) * k * k * k + 4.0 * (mx + k) * k * ps.rank;
-    flops += f;
-    svd_flops += f;
+    flops += ps.flops;
+    svd_flops += ps.flops;
     return ps.rank;
   }
 

@@ -246,6 +246,7 @@ struct SvdResult {
   int rank = -1;
   double disc = 0.0, total = 0.0;
   int sweeps = 0;
+  double solve_flops = 0.0;  // arithmetic of the block-pair solves launched
   int err = 0;  // TTM_OK or a TTM_E* code
 };
 // Runs the SVD of Y (left intact) and writes U_r into u: as U_r^T (r x no,
@@ -334,6 +335,7 @@ struct RsvdResult {
   double disc = 0.0, total = 0.0, flops = 0.0;
   double estimate = 0.0;  // the subspace-error estimate of the acceptance test
   int sweeps = 0;
+  double solve_flops = 0.0;  // as SvdResult's
   bool fallback = false;
   int err = 0;
 };
@@ -356,7 +358,8 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
 // workspace, whose size (svd_ws_doubles of the full SVD) is enough here.
 struct PsvdResult {
   int rank = -1;
-  double disc = 0.0, total = 0.0;
+  double disc = 0.0, total = 0.0, flops = 0.0;
+  double solve_flops = 0.0;  // as SvdResult's, refused results included
   double missed = 0.0;  // ||(I - Z Z^T) Theta V_r||_F / ||Theta||_F
   int sweeps = 0, filters = 0;
   bool fallback = false;
