@@ -230,15 +230,16 @@ def main():
         rot_ms = sum(s["kernel_ms"]["jacobi_solve"] for s in pstats)
         rot_n = sum(s["kernel_launches"]["jacobi_solve"] for s in pstats)
         tot_ms = sum(sum(s["kernel_ms"].values()) for s in pstats)
-        # Algorithmic SVD flops of the product, attributed to the launches of
-        # its dominant kernel (one launch = one round of one Jacobi sweep of
-        # one SVD: every block pair's Gram diagonalised, V rotated).
-        flops_per_launch = sum(s["svd_model_flops"] for s in pstats) / rot_n
-        own_per_launch = sum(s["jacobi_solve_flops"] for s in pstats) / rot_n
+        kernel_share = {k: sum(s["kernel_ms"][k] for s in pstats) / tot_ms for k in st["kernel_ms"]}
+    if prof and rot_n:
+        # The dominant kernel: one launch = one round of one Jacobi sweep of
+        # one SVD (every block pair's Gram diagonalised, its rotation formed).
+        # Its own arithmetic, FP64 vector ALU work (plane rotations of the
+        # pair Gram in LDS), over its launches: bound by latency, so its bound
+        # is the ALU peak.
+        flops_per_launch = sum(s["jacobi_solve_flops"] for s in pstats) / rot_n
         avg_launch_s = rot_ms / rot_n / 1e3
         achieved = flops_per_launch / avg_launch_s / 1e12
-        # The solve kernel's arithmetic is FP64 vector ALU work (plane
-        # rotations of the pair Gram in LDS), so its bound is the ALU peak.
         roofline = {
             "bound": "alu",
             "kernel": "jacobi_solve_kernel",
@@ -249,21 +250,15 @@ def main():
             "traffic": _measured_traffic("jacobi_solve_kernel"),
             "launches_per_step": rot_n / args.steps,
             "avg_launch_us": avg_launch_s * 1e6,
-            "algorithmic_flops_per_launch": flops_per_launch,
+            "flops_per_launch": flops_per_launch,
             "profiled_ms_per_step": 1e3 * tp / args.steps,
-            # Context for the accounting above, which credits the product's
-            # SVD model flops to the solve launches: the solve kernel's own
-            # arithmetic (it diagonalises small pair Grams in LDS: latency
-            # bound), and the whole product's model flops against the FP64
-            # matrix-core peak.
-            "kernel_own_flops_per_launch": own_per_launch,
-            "kernel_own_frac": own_per_launch / avg_launch_s / 1e12 / FP64_VALU_PEAK_TFLOPS,
+            # the whole product's flops (each SVD by the method that ran)
+            # against the FP64 matrix-core peak
             "product_algorithmic_tflops": model_flops / (ms_per_step / 1e3) / 1e12,
             "product_mfma_frac": model_flops / (ms_per_step / 1e3) / 1e12 / FP64_MFMA_PEAK_TFLOPS,
         }
         if roofline["traffic"] is not None:
             roofline["traffic_gbs"] = roofline["traffic"] / avg_launch_s / 1e9
-        kernel_share = {k: sum(s["kernel_ms"][k] for s in pstats) / tot_ms for k in st["kernel_ms"]}
 
     # The conventional chi^4 variational product of the same inputs, for comparison:
     # time per call, sweeps, and its distance from the TTM result.
@@ -306,7 +301,7 @@ def main():
                           "speedup_vs_f64": (ms_per_step / 1e3) / tr, "randomized_svds": sr["n_rsvd"],
                           "randomized_fallbacks": sr["n_rsvd_fallback"], "jacobi_sweeps": sr["sweeps"],
                           "ranks_equal_f64": sr["ranks"] == st["ranks"],
-                          "effective_fp64_mfma_frac": model_flops / tr / 1e12 / FP64_MFMA_PEAK_TFLOPS}
+                          "fp64_mfma_frac": sr["model_flops"] / tr / 1e12 / FP64_MFMA_PEAK_TFLOPS}
             _log("  %s: %.1f ms per product (%.2fx over FP64), %d randomized SVDs"
                  % (mode, 1e3 * tr, rsvd[mode]["speedup_vs_f64"], sr["n_rsvd"]))
     accuracy = None
@@ -728,9 +723,7 @@ def measure_point(cores, chi, eps, idx, dev, precisions, profile=False, steps=No
                        "sampled_rel_diff_vs_f64": float(torch.linalg.norm(gm - got) / torch.linalg.norm(got)),
                        "jacobi_sweeps": stm["sweeps"], "max_bond": stm["max_bond"],
                        "randomized_svds": stm["n_rsvd"], "randomized_fallbacks": stm["n_rsvd_fallback"],
-                       # the FP64 schedule's algorithmic flops over this mode's time: the rate at
-                       # which it delivers the same product, against the FP64 matrix peak
-                       "effective_fp64_mfma_frac": st["model_flops"] / tm / 1e12 / FP64_MFMA_PEAK_TFLOPS}
+                       "fp64_mfma_frac": stm["model_flops"] / tm / 1e12 / FP64_MFMA_PEAK_TFLOPS}
         _log("    %s: %.1f ms (%.2fx), sampled rel diff vs FP64 %.2e"
              % (prec, 1e3 * tm, dt / tm, mixed[prec]["sampled_rel_diff_vs_f64"]))
         del Cm
