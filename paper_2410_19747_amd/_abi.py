@@ -208,6 +208,12 @@ def load_library():
     if not os.path.exists(path):
         raise ImportError("libttm.so is not built (%s); run __graft_entry__.build() or "
                           "python -m paper_2410_19747_amd.build" % path)
+    # torch first: it brings a HIP runtime of its own, which libttm.so then
+    # shares; the other way round a process has two.
+    try:
+        import torch  # noqa: F401
+    except ImportError:
+        pass
     L = ctypes.CDLL(path)
     for name, (res, args) in list(PROTOTYPES.items()) + list(TESTING_PROTOTYPES.items()):
         fn = getattr(L, name)
