@@ -34,6 +34,14 @@ int ttm_test_gemm_prec(int prec, int M, int N, int K, const double *A, int64_t a
                        const double *B, int64_t b_rs, int64_t b_cs, double *C, int64_t c_rs,
                        void *stream);
 
+/* As ttm_test_gemm_prec over a batch, C = alpha A B + beta C with row stride
+ * c_rs, and with scratch of part_doubles doubles (device; null: none) that lets
+ * the product split K over workgroups as the library's own callers do. */
+int ttm_test_gemm_split(int prec, int M, int N, int K, int batch, const double *A, int64_t a_rs, int64_t a_cs,
+                        int64_t a_bs, const double *B, int64_t b_rs, int64_t b_cs, int64_t b_bs, double *C,
+                        int64_t c_rs, int64_t c_bs, double alpha, double beta, double *part, int64_t part_doubles,
+                        void *stream);
+
 /* Householder QR of the m x n row-major matrix M (device): Q (m x k,
  * row-major, k = min(m,n)) and R (k x n, row-major).  scratch: device,
  * ttm_test_qr_scratch(m, n) doubles. */
