@@ -118,9 +118,10 @@ typedef struct ttm_options {
                               in exact arithmetic) */
   int32_t svd_mode;        /* the truncated SVD of each capped swap: TTM_SVD_JACOBI (default: at full
                               accuracy, results within 1e-12 of an exact truncation; where 4 cap <=
-                              min(m, n) of the swap matrix and no ranks are forced, the cap leading
-                              triplets by a subspace iteration carried to rounding level and checked,
-                              else, or where the check refuses, the full Jacobi SVD) or
+                              min(m, n) of the swap matrix, that side is above 128 and no ranks are
+                              forced, the cap leading triplets by a subspace iteration carried to
+                              rounding level and checked, else, or where the check refuses, the full
+                              Jacobi SVD) or
                               TTM_SVD_RANDOMIZED: a subspace-iteration range finder with 2 cap
                               columns (Halko, Martinsson and Tropp 2011, Alg. 4.4) whose products
                               take the contraction precision, CholeskyQR orthonormalisation in
@@ -365,8 +366,9 @@ int ttm_multiply_vjp(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double t
 
 /* As ttm_multiply_ex and ttm_multiply_vjp, with every truncated SVD the full
  * one by the block method, whatever its size.  ttm_multiply_ex takes small
- * SVDs by one workgroup and capped swaps by a filtered subspace iteration,
- * to the same accuracy but with other rounding errors; a gradient through a truncation
+ * SVDs by one workgroup and capped swaps by a filtered subspace iteration, and
+ * ttm_multiply_vjp the adjoint of the latter from the kept triplets, to the
+ * same accuracy but with other rounding errors; a gradient through a truncation
  * amplifies those by max sigma_1^2 / (sigma_r^2 - sigma_{r+1}^2), so a
  * caller who compares gradients between versions keeps to one method.  Cbar
  * of ttm_multiply_block_vjp belongs to the C that ttm_multiply_block gives,

@@ -497,14 +497,13 @@ def _make_inner_loss_function():
 
     class TTMInnerLoss(torch.autograd.Function):
         """loss = <W, TTM(A, B)> with W fixed.  Forward: the TTM product
-        (ttm_multiply_ex), then <W, C> (ttm_inner_grad against the all-ones
+        (ttm_multiply_block), then <W, C> (ttm_inner_grad against the all-ones
         train).  Backward: dL/dC = the gradient of <W, C> with respect to C's
         cores (ttm_inner_grad_ex, environments recomputed from W and C, with
         checkpoints every ceil(sqrt(N)) sites and the others rebuilt one
-        segment at a time), then
-        the reverse mode of the product (ttm_multiply_vjp), which recomputes
-        the product with every step recorded and undoes the steps, truncated
-        SVDs included.  Only the inputs and C are kept from the forward pass.
+        segment at a time), then the reverse mode of the product
+        (ttm_multiply_block_vjp), which recomputes the product with every step
+        recorded and undoes the steps, truncated SVDs included.  Only the inputs and C are kept from the forward pass.
         Both directions take every SVD by the block method: the gradient
         amplifies an SVD's rounding errors, so they stay those of one method."""
 

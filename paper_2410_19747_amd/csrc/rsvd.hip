@@ -487,8 +487,10 @@ CqrBufs cqr_carve(int l, double *base, int64_t part = kGramPart) {
 // With want_r, b.Rf holds all of R afterwards (row-major, zero below the
 // diagonal); otherwise only its blocks right of the diagonal blocks.
 // With a shift, shift times each column's squared norm is added to the Gram's
-// diagonal: no pivot breaks down, and Q is orthonormal only as far as the
-// shift allows (further passes make it so).
+// diagonal, and Q is orthonormal only as far as the shift allows (further passes
+// make it so).  A pivot then stands unless its column is zero or the Gram's own
+// rounding, p u at worst, reaches the shift (1e-12 near 8192 rows); one that
+// does not raises the flag like any other, and the full SVD runs.
 hipError_t cholqr(double *Y, int p, int l, double *Q, const CqrBufs &b, int *fail, hipStream_t s,
                   KernelTimer *timer, bool want_r = false, double shift = 0.0) {
   Timed tm(timer, KC_QR, s);
@@ -696,11 +698,11 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
   // B = Q_B R_B by CholeskyQR2 with R_B = R2 R1 kept (Q_B is not needed):
   // B's right singular vectors and values are R_B's, and the Jacobi SVD then
   // runs on the l x l R_B instead of the m x l B.
-  // Above 128 columns it runs on R_B^T as it is: Y is ordered by the power
-  // iterations, so B's columns, and more so R_B's rows, are near orthogonal,
-  // and R_B^T needs neither a QR nor the sweeps of a general matrix (256^3
-  // product at bond 128, randomized: 191 -> 156 ms).  Up to 128 columns one
-  // launch does QR and Jacobi.
+  // Above kColumnsSmall columns it runs on R_B^T as it is: Y is ordered by the
+  // power iterations, so B's columns, and more so R_B's rows, are near
+  // orthogonal, and R_B^T needs neither a QR nor the sweeps of a general matrix
+  // (256^3 product at bond 128, randomized: 191 -> 156 ms).  Up to kColumnsSmall
+  // one launch does QR and Jacobi.
   const bool wide = l > kColumnsSmall;
   if (!ok(launch_zero_int(b.fail2, 1, s))) return out;
   if (!ok(cholqr(b.B, m, l, spare, b.cq, b.fail2, s, timer, true))) return out;
@@ -841,10 +843,14 @@ RsvdResult rsvd_oside(const double *Theta, int m, int n, int cap, int power, dou
 // by 1e-6, where the spectrum is too flat for MAX_FILTER filters, and where the
 // cap lies below the noise level.  Where a Cholesky pivot breaks down (a
 // spectrum that falls by more than about 1e7 over the l columns) the iteration
-// starts again with shifted passes (see STEEP_SHIFT).
+// starts again with shifted passes (see STEEP_SHIFT), or, if the pivots show that
+// it would find the cap below the noise level, leaves the swap to the full SVD.
 namespace {
 constexpr int PSVD_POWER = 2;     // plain iterations before the filter
-constexpr int MAX_FILTER = 10;    // beyond it the full SVD costs no more
+// Well below where the full SVD costs as much, by measurement of flatter spectra
+// at caps of a quarter and an eighth of the side: 16 and 28 filters at 160 x 160,
+// 26 and 44 at 256, 38 and 66 at 512, 38 and 98 at 1024, 36 and 82 at 2048.
+constexpr int MAX_FILTER = 10;
 // A spectrum that falls by more than about 1e7 over the sketch breaks a
 // CholeskyQR down.  The swap then starts again with half steps Y -> Theta Y ->
 // Theta^T Theta Y, each orthonormalised by two passes with this shift of the
@@ -904,7 +910,11 @@ int64_t psvd_part_doubles(int m, int n, int cap) {
 
 bool psvd_eligible(int m, int n, int cap) {
   if (!rsvd_eligible(m, n, cap)) return false;
-  if (std::min(m, n) <= kSvdSmallSide) return false;  // one launch does the full SVD
+  // One launch does the full SVD.  Measured at sides of 72 to 128 (times the
+  // same or four times that) with caps of a quarter and an eighth: 0.97 to 1.25
+  // ms at 96 and 128 for values falling as i^-1 and i^-2, here 0.90 to 1.3 and
+  // 0.72 to 1.1; for i^-3, whose sketch a quarter breaks down, here 2.2 to 2.6.
+  if (std::min(m, n) <= kSvdSmallSide) return false;
   const int l = rsvd_sketch_cols(cap);
   if (n > kSvdMaxSide || m > kSvdMaxSide) return false;
   // the discarded weight is summed over at most six blocks of columns
