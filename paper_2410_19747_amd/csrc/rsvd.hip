@@ -864,19 +864,23 @@ constexpr double STEEP_SHIFT = 1e-12;
 
 // Whether the cap lies below noise (of the largest value) in a spectrum whose
 // sketch of l columns breaks a CholeskyQR down, by the pivots (over their
-// columns' norms, 1 where they broke) of the start: the first r0 < cap stand,
-// falling as sigma^2 does.  Either they fall at a rate that takes them below
-// noise^2 by the cap, or the last of them stands four digits above the level of
-// breakdown, so that the values end there.  The shifted passes would then end
-// in a refusal by the noise level: products of rank 9 and 16 at caps 40 and 64
-// (6 sites of 8) took 31.5 and 39 ms with them, 23.4 and 34 without.
+// columns' norms, 1 where they broke) of the start, which fall as sigma^2 does:
+// r0 of them stand, and if the values go on falling half as fast as over the last
+// four digits above the level of breakdown, in which nb of the pivots lie, they
+// are below noise^2 before the cap (half: the spectra of products flatten, and a
+// swap that the shifted passes could have carried costs more than one that they
+// could not).  Where the rank ends nb is next to none.  The shifted passes would
+// then end in a refusal by the noise level: products of rank 9 and 16 at caps 40
+// and 64 (6 sites of 8) took 31.5 and 39 ms with them, 23 and 34 without.
 bool cap_in_noise(const std::vector<double> &pivots, int cap, double noise) {
   constexpr double LEVEL = 64.0 * kU;
-  int r0 = 1;
-  while (r0 < (int)pivots.size() && pivots[r0] < 1.0 - 1e-9) ++r0;
-  if (r0 >= cap) return false;
-  const double last = pivots[r0 - 1];
-  return last > 1e4 * LEVEL || pow(last, (double)cap / r0) < noise * noise;
+  int r0 = 1, above = 1;
+  while (r0 < (int)pivots.size() && pivots[r0] < 1.0 - 1e-9) {
+    if (above == r0 && pivots[r0] > 1e4 * LEVEL) ++above;
+    ++r0;
+  }
+  const int nb = r0 - above;
+  return r0 < cap && 4.0 * (cap - r0) > 2.0 * nb * log10(LEVEL / (noise * noise));
 }
 
 struct PsvdBufs {

@@ -27,10 +27,11 @@ def _host(packed):
     return [c.detach().cpu().numpy() for c in packed.cores()]
 
 
-@pytest.mark.parametrize("rank,chi,cap", [(3, 32, 40), (4, 64, 64), (2, 30, 33)])
+@pytest.mark.parametrize("rank,chi,cap", [(3, 32, 40), (4, 64, 100), (2, 30, 33)])
 def test_low_rank_costs_one_start(rank, chi, cap):
-    """Products and factorisations (timed regions): at most those of the block
-    method and of one start a swap (five products, three orthonormalisations)."""
+    """Products and factorisations (timed regions) where every swap's rank lies
+    below the cap: at most those of the block method and of one start a swap
+    (five products, three orthonormalisations)."""
     import paper_2410_19747_amd as T
 
     A, B = _padded(6, 8, chi, rank, 7), _padded(6, 8, chi, rank, 8)
