@@ -364,8 +364,9 @@ int ttm_multiply_vjp(const ttm_tt *A, const ttm_tt *B, int32_t chi_out, double t
                      const ttm_tt *Cbar, ttm_tt_out *C, double *dA, double *dB, void *ws, size_t ws_bytes,
                      void *stream, ttm_stats *stats);
 
-/* As ttm_multiply_ex and ttm_multiply_vjp, with every truncated SVD the full
- * one by the block method, whatever its size.  ttm_multiply_ex takes small
+/* As ttm_multiply_ex and ttm_multiply_vjp, with every truncated SVD of
+ * svd_mode TTM_SVD_JACOBI the full one by the block method, whatever its size
+ * (TTM_SVD_RANDOMIZED: as there).  ttm_multiply_ex takes small
  * SVDs by one workgroup and capped swaps by a filtered subspace iteration, and
  * ttm_multiply_vjp the adjoint of the latter from the kept triplets, to the
  * same accuracy but with other rounding errors; a gradient through a truncation
